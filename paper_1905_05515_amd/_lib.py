@@ -130,6 +130,7 @@ EXPORTS = {
     "tpc_fit_merged_tracks": (C.c_int, [P, C.POINTER(Problem), Clusters, Tracklets, Tracks, P,
                                         P, P, P, I32, F32, F32, I32, F32, FitOut, P]),
     "tpc_track_t0": (C.c_int, [P, C.POINTER(Problem), Tracklets, Tracks, P, F32, P, P, P, P, P]),
+    "tpc_check_exact_fp32": (C.c_int, [C.c_int, C.c_uint32, C.c_uint32, P, P]),
     "tpc_status_string": (C.c_char_p, [C.c_int]),
     "tpc_timing_enable": (C.c_int, [P, C.c_int]),
     "tpc_timing_report": (C.c_int, [P, C.c_int, C.POINTER(C.c_char_p), C.POINTER(I64),

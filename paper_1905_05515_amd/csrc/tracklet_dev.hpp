@@ -12,6 +12,7 @@
 // rounding); with contraction off otherwise and IEEE division and square
 // root the results are the same bits on any conforming implementation.
 #pragma once
+#include "exact_fp32.hpp"
 #include "tpc_internal.hpp"
 
 namespace tpc {
@@ -33,21 +34,39 @@ __device__ __forceinline__ bool propagate(KState& st, float dx, float curv, floa
     const float k = curv * w;
     const float s2 = fmaf(k, dx, s);
     if (!(fabsf(s) < s_max) || !(fabsf(s2) < s_max)) return false;
-    const float c1 = sqrtf((1.0f - s) * (1.0f + s));
-    const float c2 = sqrtf((1.0f - s2) * (1.0f + s2));
-    const float cc = c1 + c2;
-    const float icc = 1.0f / cc;   // one reciprocal for the three quotients by cc
-    const float T = (s + s2) * icc;
-    const float q = sqrtf(fmaf(T, T, 1.0f));
+    const float u1 = (1.0f - s) * (1.0f + s), u2 = (1.0f - s2) * (1.0f + s2);
+    // one reciprocal of cc = c1 + c2 for the three quotients by it
+    float icc, T, q, e1, e2, Tq;   // e1 = s / c1, e2 = s2 / c2, Tq = T / q
+    if (s_max <= 1.0f) {
+        // |s| < 1 keeps every operand where the short sequences are the
+        // correctly rounded operations (u >= 2^-24; a quotient e too small
+        // for them vanishes beside the 1 or 2 it is added to, and T / q = T
+        // there, q being 1)
+        const float c1 = sqrt_exact(u1), c2 = sqrt_exact(u2);
+        icc = rcp_exact(c1 + c2);
+        e1 = div_exact(s, c1, rcp_exact(c1));
+        e2 = div_exact(s2, c2, rcp_exact(c2));
+        T = (s + s2) * icc;
+        q = sqrt_exact(fmaf(T, T, 1.0f));
+        Tq = copysignf(div_exact(T, q, rcp_exact(q)), T);
+    } else {
+        const float c1 = sqrtf(u1), c2 = sqrtf(u2);
+        icc = 1.0f / (c1 + c2);
+        e1 = s / c1;
+        e2 = s2 / c2;
+        T = (s + s2) * icc;
+        q = sqrtf(fmaf(T, T, 1.0f));
+        Tq = T / q;
+    }
     const float L = dx * q;
     const float a = 0.5f * (k * L);
     const float a2 = a * a;
     const float g = fmaf(a2, fmaf(a2, fmaf(a2, 5.0f / 112.0f, 3.0f / 40.0f), 1.0f / 6.0f), 1.0f);
     const float S = L * g;
-    const float Ts = fmaf(T, s / c1 + s2 / c2, 2.0f) * icc;
+    const float Ts = fmaf(T, e1 + e2, 2.0f) * icc;
     const float kdx = curv * dx;
-    const float Tw = (kdx * fmaf(T, s2 / c2, 1.0f)) * icc;
-    const float LT = dx * (T / q);
+    const float Tw = (kdx * fmaf(T, e2, 1.0f)) * icc;
+    const float LT = dx * Tq;
     const float G1 = fmaf(a2, fmaf(a2, fmaf(a2, 5.0f / 16.0f, 3.0f / 8.0f), 0.5f), 1.0f);
     const float Sk = (L * (L * a)) * fmaf(a2, fmaf(a2, 15.0f / 112.0f, 3.0f / 20.0f), 1.0f / 6.0f);
     const float Fys = dx * Ts;
@@ -84,23 +103,31 @@ __device__ __forceinline__ bool propagate(KState& st, float dx, float curv, floa
     return true;
 }
 
-__device__ __forceinline__ float chi2_pred(const KState& st, float my, float mz, float sy2, float sz2)
+// Inverse covariance of the predicted measurement, B = S^-1 with
+// S = C_yz + diag(sy2, sz2): one per row step, for every candidate's chi2
+// and for the update.
+struct Gain {
+    float B00, B10, B11;
+};
+
+__device__ __forceinline__ Gain gain_of(const KState& st, float sy2, float sz2)
 {
-    const float r0 = my - st.p[0], r1 = mz - st.p[1];
     const float S00 = st.C[0] + sy2, S10 = st.C[1], S11 = st.C[2] + sz2;
     const float det = fmaf(S00, S11, -(S10 * S10));
-    const float idet = 1.0f / det;
-    const float B00 = S11 * idet, B10 = -(S10 * idet), B11 = S00 * idet;
-    return fmaf(r1, fmaf(B11, r1, B10 * r0), r0 * fmaf(B10, r1, B00 * r0));
+    const float idet = rcp_any(det);
+    return {S11 * idet, -(S10 * idet), S00 * idet};
 }
 
-__device__ __forceinline__ float kupdate(KState& st, float my, float mz, float sy2, float sz2)
+__device__ __forceinline__ float chi2_pred(const KState& st, const Gain& g, float my, float mz)
 {
     const float r0 = my - st.p[0], r1 = mz - st.p[1];
-    const float S00 = st.C[0] + sy2, S10 = st.C[1], S11 = st.C[2] + sz2;
-    const float det = fmaf(S00, S11, -(S10 * S10));
-    const float idet = 1.0f / det;
-    const float B00 = S11 * idet, B10 = -(S10 * idet), B11 = S00 * idet;
+    return fmaf(r1, fmaf(g.B11, r1, g.B10 * r0), r0 * fmaf(g.B10, r1, g.B00 * r0));
+}
+
+__device__ __forceinline__ float kupdate(KState& st, const Gain& g, float my, float mz)
+{
+    const float r0 = my - st.p[0], r1 = mz - st.p[1];
+    const float B00 = g.B00, B10 = g.B10, B11 = g.B11;
     const float chi2 = fmaf(r1, fmaf(B11, r1, B10 * r0), r0 * fmaf(B10, r1, B00 * r0));
     float A0[5], A1[5], K0[5], K1[5];
 #pragma unroll
@@ -123,6 +150,11 @@ __device__ __forceinline__ float kupdate(KState& st, float my, float mz, float s
     return chi2;
 }
 
+__device__ __forceinline__ float kupdate(KState& st, float my, float mz, float sy2, float sz2)
+{
+    return kupdate(st, gain_of(st, sy2, sz2), my, mz);
+}
+
 __device__ __forceinline__ void reset_cov(KState& st, const tpc_params& prm)
 {
 #pragma unroll
@@ -141,7 +173,7 @@ constexpr int kCandBatch = 4;   // candidate loads issued together
 // in (my, mz).  The bins scanned cover +-nsigma of the prediction (every hit
 // passing the gate lies inside); the gate decides.  Two z rows of bins are
 // opened at a time so that their bin bounds load together.
-__device__ __forceinline__ int search_row(const KState& st, const tpc_sector& s, int r,
+__device__ __forceinline__ int search_row(const KState& st, const Gain& G, const tpc_sector& s, int r,
                                           const tpc_params& prm, int& n_cand,
                                           const int32_t* __restrict__ bin_start,
                                           const float* __restrict__ yg,
@@ -192,7 +224,7 @@ __device__ __forceinline__ int search_row(const KState& st, const tpc_sector& s,
 #pragma unroll
             for (int j = 0; j < kCandBatch; ++j) {
                 if (b + j >= n0 + n1) break;
-                const float c2 = chi2_pred(st, yb[j], zb[j], prm.sigma_y2, prm.sigma_z2);
+                const float c2 = chi2_pred(st, G, yb[j], zb[j]);
                 if (!(c2 <= prm.chi2_max)) continue;
                 // equal chi2 (rare): the lower cluster id wins
                 if (bpos < 0 || c2 < best || (c2 == best && idg[pb[j]] < idg[bpos])) {
@@ -269,22 +301,21 @@ __device__ __forceinline__ void build_tracklet(
         }
         ++n_prop;
         if (!propagate(st, xs[r] - xs[r - 1], prm.curv, prm.s_max)) break;
+        const Gain G = gain_of(st, sy2, sz2);
         int c = cc;
         float my = cy, mz = cz;
-        if (!chain) {
-            c = search_row(st, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
-            if (c < 0) {
-                if (++miss >= prm.max_miss) break;
-                continue;
-            }
+        if (!chain) c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
+        if (c >= 0) {
+            ++n_upd;
+            kupdate(st, G, my, mz);
+            th[r * ths] = c;
+            last = r;
             miss = 0;
-        }
-        ++n_upd;
-        kupdate(st, my, mz, sy2, sz2);
-        th[r * ths] = c;
-        last = r;
 #pragma unroll
-        for (int i = 0; i < 5; ++i) plast[i] = st.p[i];
+            for (int i = 0; i < 5; ++i) plast[i] = st.p[i];
+        } else if (++miss >= prm.max_miss) {
+            break;
+        }
         if (chain) {
             cc = cn;
             cy = ny;
@@ -333,20 +364,17 @@ __device__ __forceinline__ void build_tracklet(
             for (int q = r; q >= 0; --q) th[q * ths] = -1;
             break;
         }
-        if (r < r0) {
-            c = search_row(st, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
-            if (c < 0) {
-                if (++miss >= prm.max_miss) break;
-                continue;
-            }
-            miss = 0;
-        }
+        const Gain G = gain_of(st, sy2, sz2);
+        if (r < r0) c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
         if (c >= 0) {
             ++n_upd;
-            csum = csum + kupdate(st, my, mz, sy2, sz2);
+            csum = csum + kupdate(st, G, my, mz);
             th[r * ths] = c;
             rin = r;
+            miss = 0;
             in = st;
+        } else if (r < r0 && ++miss >= prm.max_miss) {
+            break;
         }
     }
     int nh = 0;
@@ -505,9 +533,10 @@ __device__ __forceinline__ void lane_step(LaneTracklet& L, int n_rows, const flo
         }
         return;
     }
+    const Gain G = gain_of(L.st, prm.sigma_y2, prm.sigma_z2);
     const bool search = upp ? c < 0 : r < L.r0;
     if (search) {
-        c = search_row(L.st, L.s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
+        c = search_row(L.st, G, L.s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
         if (c < 0) {
             if (++L.miss >= prm.max_miss) {
                 if (upp) lane_begin_down(L, prm, yg, zg, cap);
@@ -520,7 +549,7 @@ __device__ __forceinline__ void lane_step(LaneTracklet& L, int n_rows, const flo
     }
     if (c >= 0) {
         ++n_upd;
-        const float chi = kupdate(L.st, my, mz, prm.sigma_y2, prm.sigma_z2);
+        const float chi = kupdate(L.st, G, my, mz);
         L.th[(int64_t)r * cap] = c;
         if (upp) {
             L.last = r;
