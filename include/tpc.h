@@ -203,15 +203,10 @@ int tpc_context_create(tpc_context** out, int device);
 int tpc_context_destroy(tpc_context* ctx);
 
 /* Launch shapes of a context (none changes any output; every field 0 is
- * the library's own choice).  tracklet_form: how tpc_construct_tracklets
- * holds the hit lists while it builds them and deals the starts to
- * waves: TPC_TRACKLETS_LDS (one LDS column per lane, written out at the
- * end), TPC_TRACKLETS_DIRECT (written into the output as found) or
- * TPC_TRACKLETS_QUEUE (written directly; resident waves whose lanes take a
- * new start from a device queue whenever theirs is done); automatic takes
- * the LDS form while all its waves are resident at once, else the direct
- * form.  neighbour_block: threads per block
- * of the neighbour kernel (64, 128 or 256).  persistent_scale: tile size
+ * the library's own choice).  tracklet_form: one of
+ * the values below; all of them select the one form there is (the hit lists
+ * written row by row as the waves walk the rows).  neighbour_block: threads
+ * per block of the neighbour kernel (64, 128 or 256).  persistent_scale: tile size
  * multiplier of the persistent form (1, 2, 4 or 8; automatic grows it with
  * the clusters per resident block).  persistent_blocks_per_cu: blocks of
  * the persistent launch per compute unit (at most the resident count;

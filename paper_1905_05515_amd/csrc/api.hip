@@ -82,8 +82,7 @@ int tpc_construct_tracklets(tpc_context* ctx, const tpc_problem* h_prob, tpc_gri
     if (!grid_ok(grid) || !links_ok(links) || !starts_ok(starts) || !trl_ok(tracklets, starts))
         return TPC_ERR_INVALID_ARG;
     return tpc::run_construct_tracklets(h_prob, 0, h_prob->n_sectors, grid, links, starts,
-                                        tracklets, ws, (hipStream_t)stream,
-                                        ctx ? &ctx->tune : nullptr);
+                                        tracklets, ws, (hipStream_t)stream);
 }
 
 int tpc_select_tracks(tpc_context* ctx, const tpc_problem* h_prob, tpc_grid grid,
@@ -132,7 +131,7 @@ int tpc_track_batch(tpc_context* ctx, const tpc_problem* h_prob, tpc_clusters in
                 r = tpc::run_find_neighbours(h_prob, 0, ns, grid, links, starts, ws, st, tune);
             if (!r)
                 r = tpc::run_construct_tracklets(h_prob, 0, ns, grid, links, starts, tracklets,
-                                                 ws, st, tune);
+                                                 ws, st);
             if (!r) r = tpc::run_select_tracks(h_prob, grid, count_cap, tracklets, tracks, ws, st);
         } else if (mode == TPC_MODE_PER_SECTOR) {
             // every stage sector by sector, then one dense compaction of the
@@ -145,7 +144,7 @@ int tpc_track_batch(tpc_context* ctx, const tpc_problem* h_prob, tpc_clusters in
                                                  tune);
                 if (!r)
                     r = tpc::run_construct_tracklets(h_prob, s, s + 1, grid, links, starts,
-                                                     tracklets, ws, st, tune);
+                                                     tracklets, ws, st);
                 if (!r) r = tpc::run_select_keys(h_prob, s, s + 1, grid, count_cap, tracklets, ws, st);
             }
             if (!r) r = tpc::run_select_compact(h_prob, grid, count_cap, tracklets, tracks, ws, st);

@@ -129,10 +129,11 @@ __global__ void k_persist_setup(Workspace ws, int n_sec)
 // sector's chunk counter: every wave of every tracklet task of the sector
 // takes the next chunk as soon as it is done with its own (tracklet lengths
 // vary a lot, and the static task count only bounds the sector's starts).
-__device__ __forceinline__ void tracklet_task(const PArgs& a, const float* xs, int32_t* next,
-                                              int64_t lo, int64_t hi)
+__device__ __forceinline__ void tracklet_task(const PArgs& a, const float* xs, float4* keep,
+                                              int32_t* next, int64_t lo, int64_t hi)
 {
     const int lane = threadIdx.x & (kWave - 1);
+    keep += (threadIdx.x / kWave) * kKeepVec + lane;
     int n_prop = 0, n_upd = 0, n_cand = 0;
     for (;;) {
         int c = 0;
@@ -141,11 +142,11 @@ __device__ __forceinline__ void tracklet_task(const PArgs& a, const float* xs, i
         const int64_t tb = lo + (int64_t)c * kWave;
         if (tb >= hi) break;
         const int64_t t = tb + lane;
-        if (t < hi)
-            build_tracklet(t, a.sec, a.n_rows, xs, a.prm, a.grid.bin_start, a.grid.y, a.grid.z,
-                           a.grid.id, a.ws.gsr, a.links.up, a.starts, a.trl.hits + t,
-                           a.trl.capacity, a.trl.start, a.trl.nhits, a.trl.row_inner, a.trl.par,
-                           a.trl.cov, a.trl.chi2, n_prop, n_upd, n_cand);
+        build_tracklets((uint32_t)t, t < hi, a.sec, a.n_rows, xs, a.prm, a.grid.bin_start,
+                        a.grid.y, a.grid.z, a.grid.id, a.ws.gsr, a.links.up, a.starts,
+                        a.trl.hits, a.trl.capacity, keep, a.trl.start, a.trl.nhits,
+                        a.trl.row_inner, a.trl.par, a.trl.cov, a.trl.chi2, n_prop, n_upd,
+                        n_cand);
     }
     add_work(a.ws.status, n_prop, n_upd, n_cand);
 }
@@ -173,7 +174,7 @@ void k_persistent(PArgs a)
     __shared__ int64_t lds64[kBlock / kWave];
     __shared__ uint64_t ldsu[kBlock / kWave];
     __shared__ int red[kBlock / kWave];
-    __shared__ unsigned long long pbuf[kPersistLds];
+    __shared__ __align__(16) unsigned long long pbuf[kPersistLds];
     int* ibuf = reinterpret_cast<int*>(pbuf);
     for (int i = threadIdx.x; i < a.n_rows; i += blockDim.x) xs[i] = a.row_x[i];
     const int n_sec = a.n_sec, n_rows = a.n_rows, S = a.S;
@@ -387,7 +388,8 @@ void k_persistent(PArgs a)
             break;
         }
         case P_TRACKLET:
-            tracklet_task(a, xs, a.ws.pchunk + si, t_lo, t_hi);
+            static_assert(kBlock / kWave * kKeepVec * 2 <= kPersistLds, "kept states");
+            tracklet_task(a, xs, reinterpret_cast<float4*>(pbuf), a.ws.pchunk + si, t_lo, t_hi);
             break;
         case P_SELCHUNK:
             sel_chunk_block(s, tile, n_rows, a.prm, a.grid.bin_start, a.grid.id, a.trl.start,

@@ -50,7 +50,6 @@ struct Workspace {
     uint64_t* tsum;        // persistent form: [n_sectors] tracks << 32 | hits per sector
     int64_t* ptile;        // persistent form: starts per counting tile
     int32_t* pchunk;       // persistent form: [n_sectors] next tracklet chunk of each sector
-    uint64_t* tq;          // [8] queue form of the tracklets: starts taken per XCD share
     int32_t* tpos;         // [n] selection: grid position of every track hit, in track order
     size_t bytes;
 };
@@ -222,8 +221,7 @@ int run_find_neighbours(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid g
                         hipStream_t st, const tpc_tuning* tune = nullptr);
 int run_construct_tracklets(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
                             tpc_links links, tpc_starts starts, tpc_tracklets trl,
-                            const Workspace& ws, hipStream_t st,
-                            const tpc_tuning* tune = nullptr);
+                            const Workspace& ws, hipStream_t st);
 int run_select_keys(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
                     int64_t count_cap, tpc_tracklets trl, const Workspace& ws, hipStream_t st);
 int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,

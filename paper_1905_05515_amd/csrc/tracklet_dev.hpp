@@ -28,12 +28,19 @@ struct KState {
 // |sin(phi)| at either end of the step is not below s_max: at the far end
 // the track turns back before the plane, at the near end an update has
 // pushed the state out of the transport's domain (|s| >= 1 has no cosine).
-__device__ __forceinline__ bool propagate(KState& st, float dx, float curv, float s_max)
+__device__ __forceinline__ bool can_propagate(const KState& st, float dx, float curv, float s_max)
+{
+    const float s = st.p[2];
+    const float s2 = fmaf(curv * st.p[4], dx, s);
+    return fabsf(s) < s_max && fabsf(s2) < s_max;
+}
+
+// the transport where it is possible
+__device__ __forceinline__ void transport(KState& st, float dx, float curv, float s_max)
 {
     const float s = st.p[2], t = st.p[3], w = st.p[4];
     const float k = curv * w;
     const float s2 = fmaf(k, dx, s);
-    if (!(fabsf(s) < s_max) || !(fabsf(s2) < s_max)) return false;
     const float u1 = (1.0f - s) * (1.0f + s), u2 = (1.0f - s2) * (1.0f + s2);
     // one reciprocal of cc = c1 + c2 for the three quotients by it
     float icc, T, q, e1, e2, Tq;   // e1 = s / c1, e2 = s2 / c2, Tq = T / q
@@ -100,7 +107,13 @@ __device__ __forceinline__ bool propagate(KState& st, float dx, float curv, floa
     st.p[0] = fmaf(dx, T, st.p[0]);
     st.p[1] = fmaf(t, S, st.p[1]);
     st.p[2] = s2;
-    return true;
+}
+
+__device__ __forceinline__ bool propagate(KState& st, float dx, float curv, float s_max)
+{
+    const bool ok = can_propagate(st, dx, curv, s_max);
+    if (ok) transport(st, dx, curv, s_max);
+    return ok;
 }
 
 // Inverse covariance of the predicted measurement, B = S^-1 with
@@ -239,359 +252,252 @@ __device__ __forceinline__ int search_row(const KState& st, const Gain& G, const
     return bpos;
 }
 
-// Build tracklet t (one thread).  xs holds the row positions; the hit list
-// (grid position per row, -1 where none) goes to th[r * ths], which is either
-// the tracklet's column of the [row][tracklet] output or a scratch column in
-// LDS that the caller copies out.
+__device__ __forceinline__ int wave_min(int v)
+{
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const int w = __shfl_xor(v, o, kWave);
+        v = w < v ? w : v;
+    }
+    return v;
+}
+
+// LDS of one wave of build_tracklets: the state after the last update of
+// every lane's inward pass, five float4 per lane.  (Kept in registers it
+// cost a copy of 20 registers per row, and as many again where the branches
+// of a row meet.)
+constexpr int kKeepVec = 5 * kWave;
+
+__device__ __forceinline__ void keep_state(float4* keep, const KState& st)
+{
+    keep[0 * kWave] = make_float4(st.p[0], st.p[1], st.p[2], st.p[3]);
+    keep[1 * kWave] = make_float4(st.p[4], st.C[0], st.C[1], st.C[2]);
+    keep[2 * kWave] = make_float4(st.C[3], st.C[4], st.C[5], st.C[6]);
+    keep[3 * kWave] = make_float4(st.C[7], st.C[8], st.C[9], st.C[10]);
+    keep[4 * kWave] = make_float4(st.C[11], st.C[12], st.C[13], st.C[14]);
+}
+
+// Build the tracklets of one wave, tracklet t in each lane with `act` (every
+// lane of the wave calls).  xs holds the row positions; the hit list (grid
+// position per row, -1 where none) is column t of t_hits[row][cap]; keep:
+// the lane's slot of kKeepVec float4 in LDS.
 //
 // Up pass: from the start hit, one row at a time, the next hit is the next
 // link of the chain while there is one (links always join adjacent rows),
 // then the least-chi2 hit of a window search.  Down pass: from the outermost
 // hit with the initial covariance, the hits already assigned are refitted and
 // rows below the start are searched.  The loads of the next chain hit (up
-// pass) and of the next assigned hit (down pass) are issued one row ahead.
-__device__ __forceinline__ void build_tracklet(
-    int64_t t, const tpc_sector* __restrict__ sec, int n_rows, const float* xs,
+// pass) are issued one row ahead; in the down pass the hit list entry of row
+// r - 2 loads during row r and the coordinates of the hit of row r - 1
+// during row r, so that no step waits on a load it issued itself.
+//
+// The wave walks the rows in step: a lane joins the up pass at the row above
+// its start and the down pass at its outermost hit.  Some lane's tracklet
+// nearly always spans the sector, so this adds few rows to the walk, and all
+// lanes then read the bins and hits of one row (a few dozen lines of L1)
+// and write one row of the hit lists as one line, where lanes each at their
+// own row read their own lines and wrote single words.
+__device__ __forceinline__ void build_tracklets(
+    uint32_t t, bool act, const tpc_sector* __restrict__ sec, int n_rows, const float* xs,
     const tpc_params& prm, const int32_t* __restrict__ bin_start, const float* __restrict__ yg,
     const float* __restrict__ zg, const int32_t* __restrict__ idg,
     const int32_t* __restrict__ gsr, const int32_t* __restrict__ up,
-    const int32_t* __restrict__ starts, int32_t* th, int64_t ths, int32_t* __restrict__ t_start,
-    int32_t* __restrict__ t_nhits, int32_t* __restrict__ t_rin,
+    const int32_t* __restrict__ starts, int32_t* t_hits, int64_t cap, float4* keep,
+    int32_t* __restrict__ t_start, int32_t* __restrict__ t_nhits, int32_t* __restrict__ t_rin,
     float* __restrict__ t_par, float* __restrict__ t_cov, float* __restrict__ t_chi2,
-    int& n_prop, int& n_upd, int& n_cand)
+    int& n_prop, int& n_upd, int& n_cand)   // of the wave; of the wave; of the lane
 {
     const float sy2 = prm.sigma_y2, sz2 = prm.sigma_z2;
-    for (int r = 0; r < n_rows; ++r) th[r * ths] = -1;
-    const int h0 = starts[t];
-    const int v0 = gsr[h0];
-    const tpc_sector s = sec[v0 >> 8];
-    const int r0 = v0 & 255;
-    const int h1 = up[h0], h2 = up[h1];
-    const int r2 = gsr[h2] & 255;
-    KState st;
-    {   // state from the first and third chain hits
-        const float dX = xs[r2] - xs[r0];
-        const float T0 = (yg[h2] - yg[h0]) / dX;
+    // a tracklet has three clusters of its own: t < 2^31 / 3, a 32-bit byte
+    // offset from the row's (uniform) base
+    const uint32_t tb = t * 4u;
+    auto hit_at = [&](int r) -> int32_t& {
+        return *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(t_hits + r * cap) + tb);
+    };
+    tpc_sector s{};
+    KState st{};
+    int r0 = n_rows;                      // a lane without a tracklet never joins
+    int cc = -1, cn = -1;                 // chain hit of the coming row, of the one after
+    float cy = 0.0f, cz = 0.0f;
+    if (act) {
+        const int h0 = starts[t];
+        const int v0 = gsr[h0];
+        s = sec[v0 >> 8];
+        r0 = v0 & 255;
+        cc = up[h0];
+        cn = up[cc];
+        // state from the first and third chain hits
+        const float dX = xs[gsr[cn] & 255] - xs[r0];
+        const float T0 = (yg[cn] - yg[h0]) / dX;
         const float q0 = sqrtf(1.0f + T0 * T0);
         st.p[0] = yg[h0];
         st.p[1] = zg[h0];
         st.p[2] = T0 / q0;
-        st.p[3] = (zg[h2] - zg[h0]) / (dX * q0);
+        st.p[3] = (zg[cn] - zg[h0]) / (dX * q0);
         st.p[4] = 0.0f;
         reset_cov(st, prm);
+        cy = yg[cc];
+        cz = zg[cc];
+        t_start[t] = h0;
+        hit_at(r0) = h0;
     }
-    th[r0 * ths] = h0;
-    int last = r0;
-    float plast[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) plast[i] = st.p[i];
+    // the up pass keeps the direction and q/pT at the outermost hit
+    *keep = make_float4(st.p[2], st.p[3], st.p[4], 0.0f);
 
     // ---- up pass
-    int cc = h1, cn = h2;                 // chain hit of this row, of the next
-    float cy = yg[h1], cz = zg[h1];
-    int miss = 0;
-    for (int r = r0 + 1; r < n_rows; ++r) {
-        const bool chain = cc >= 0;
-        float ny = 0.0f, nz = 0.0f;
-        int cnn = -1;
-        if (cn >= 0) {
-            ny = yg[cn];
-            nz = zg[cn];
-            cnn = up[cn];
+    const int r_lo = wave_min(r0);
+    int r = 0;
+    for (; r <= r_lo && r < n_rows; ++r)
+        if (act && r != r0) hit_at(r) = -1;
+    int last = r0, miss = 0, nh = 1;
+    bool go = act;
+    for (; r < n_rows && __any(go); ++r) {
+        const float dx = xs[r] - xs[r - 1];
+        int hv = -1;
+        bool upd = false;
+        const bool step = go && r > r0;
+        n_prop += __popcll(__ballot(step));
+        if (step) {
+            const bool chain = cc >= 0;
+            float ny = 0.0f, nz = 0.0f;
+            int cnn = -1;
+            if (cn >= 0) {
+                ny = yg[cn];
+                nz = zg[cn];
+                cnn = up[cn];
+            }
+            go = can_propagate(st, dx, prm.curv, prm.s_max);
+            if (go) {
+                transport(st, dx, prm.curv, prm.s_max);
+                const Gain G = gain_of(st, sy2, sz2);
+                int c = cc;
+                float my = cy, mz = cz;
+                if (!chain)
+                    c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
+                if (c >= 0) {
+                    kupdate(st, G, my, mz);
+                    *keep = make_float4(st.p[2], st.p[3], st.p[4], 0.0f);
+                    upd = true;
+                    last = r;
+                    ++nh;
+                    miss = 0;
+                } else {
+                    go = ++miss < prm.max_miss;
+                }
+                hv = c;
+                if (chain) {
+                    cc = cn;
+                    cy = ny;
+                    cz = nz;
+                    cn = cnn;
+                }
+            }
         }
-        ++n_prop;
-        if (!propagate(st, xs[r] - xs[r - 1], prm.curv, prm.s_max)) break;
-        const Gain G = gain_of(st, sy2, sz2);
-        int c = cc;
-        float my = cy, mz = cz;
-        if (!chain) c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
-        if (c >= 0) {
-            ++n_upd;
-            kupdate(st, G, my, mz);
-            th[r * ths] = c;
-            last = r;
-            miss = 0;
-#pragma unroll
-            for (int i = 0; i < 5; ++i) plast[i] = st.p[i];
-        } else if (++miss >= prm.max_miss) {
-            break;
-        }
-        if (chain) {
-            cc = cn;
-            cy = ny;
-            cz = nz;
-            cn = cnn;
-        }
+        n_upd += __popcll(__ballot(upd));
+        if (act && r != r0) hit_at(r) = hv;
     }
+    for (; r < n_rows; ++r)
+        if (act) hit_at(r) = -1;
 
     // ---- down pass
-    const int hl = th[last * ths];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) st.p[i] = plast[i];
-    st.p[0] = yg[hl];
-    st.p[1] = zg[hl];
-    reset_cov(st, prm);
-    KState in = st;
+    r = -wave_min(act ? -last : 1);
     float csum = 0.0f;
     int rin = last;
-    miss = 0;
-    // assigned hits of the next two rows down: the hit list entry of row
-    // r - 2 loads during step r, the coordinates of the hit of row r - 1
-    // during step r (its entry loaded a step before), so that no step waits
-    // on a load it issued itself
-    int an = -1, an2 = -1;
+    bool fit = false;                     // joined, and neither failed nor ended
+    // assigned hits of this row and the next one down
+    int e1 = r >= r0 ? hit_at(r) : -1, e2 = r - 1 >= r0 ? hit_at(r - 1) : -1;
     float ay = 0.0f, az = 0.0f;
-    if (last - 1 >= r0) {
-        an = th[(last - 1) * ths];
-        if (an >= 0) {
-            ay = yg[an];
-            az = zg[an];
-        }
+    if (e1 >= 0) {
+        ay = yg[e1];
+        az = zg[e1];
     }
-    if (last - 2 >= r0) an2 = th[(last - 2) * ths];
-    for (int r = last - 1; r >= 0; --r) {
-        int c = an;
+    miss = 0;
+    go = act;
+    for (; r >= 0 && __any(go); --r) {
+        const int e0 = e1;
         float my = ay, mz = az;
-        an = an2;                         // the hit of row r - 1, or -1
-        an2 = -1;
-        if (an >= 0) {
-            ay = yg[an];
-            az = zg[an];
+        e1 = e2;
+        if (e1 >= 0) {
+            ay = yg[e1];
+            az = zg[e1];
         }
-        if (r - 2 >= r0) an2 = th[(r - 2) * ths];
-        ++n_prop;
-        if (!propagate(st, xs[r] - xs[r + 1], prm.curv, prm.s_max)) {
-            for (int q = r; q >= 0; --q) th[q * ths] = -1;
-            break;
+        e2 = r - 2 >= r0 ? hit_at(r - 2) : -1;
+        bool upd = false;
+        n_prop += __popcll(__ballot(fit));
+        if (fit) {
+            const float dx = xs[r] - xs[r + 1];
+            fit = can_propagate(st, dx, prm.curv, prm.s_max);
+            if (fit) {
+                transport(st, dx, prm.curv, prm.s_max);
+                const Gain G = gain_of(st, sy2, sz2);
+                int c = e0;
+                if (r < r0)
+                    c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
+                if (c >= 0) {
+                    csum = csum + kupdate(st, G, my, mz);
+                    keep_state(keep, st);
+                    upd = true;
+                    if (r < r0) {
+                        hit_at(r) = c;
+                        ++nh;
+                    }
+                    rin = r;
+                    miss = 0;
+                } else if (r < r0) {
+                    fit = go = ++miss < prm.max_miss;
+                }
+            }
         }
-        const Gain G = gain_of(st, sy2, sz2);
-        if (r < r0) c = search_row(st, G, s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
-        if (c >= 0) {
-            ++n_upd;
-            csum = csum + kupdate(st, G, my, mz);
-            th[r * ths] = c;
-            rin = r;
-            miss = 0;
-            in = st;
-        } else if (r < r0 && ++miss >= prm.max_miss) {
-            break;
+        if (r == last) {                  // never of a lane without a tracklet: last = n_rows
+            st.p[0] = my;
+            st.p[1] = mz;
+            const float4 d = *keep;
+            st.p[2] = d.x;
+            st.p[3] = d.y;
+            st.p[4] = d.z;
+            reset_cov(st, prm);
+            keep_state(keep, st);
+            fit = true;
         }
+        // a propagation stop drops the assigned hits from here down
+        if (go && !fit && r < last) {
+            if (e0 >= 0) {
+                hit_at(r) = -1;
+                --nh;
+            }
+            go = r > r0;
+        }
+        n_upd += __popcll(__ballot(upd));
     }
-    int nh = 0;
-    for (int r = 0; r < n_rows; ++r) nh += th[r * ths] >= 0;
-    t_start[t] = h0;
+    if (!act) return;
     t_nhits[t] = nh;
     t_rin[t] = rin;
+    float v[20];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) t_par[t * 5 + i] = in.p[i];
+    for (int q = 0; q < 5; ++q) {
+        const float4 k = keep[q * kWave];
+        v[4 * q] = k.x;
+        v[4 * q + 1] = k.y;
+        v[4 * q + 2] = k.z;
+        v[4 * q + 3] = k.w;
+    }
 #pragma unroll
-    for (int i = 0; i < 15; ++i) t_cov[t * 15 + i] = in.C[i];
+    for (int i = 0; i < 5; ++i) t_par[(int64_t)t * 5 + i] = v[i];
+#pragma unroll
+    for (int i = 0; i < 15; ++i) t_cov[(int64_t)t * 15 + i] = v[5 + i];
     t_chi2[t] = csum;
 }
 
-// ---- queue form ------------------------------------------------------------
-// One thread per tracklet at a time, every lane at its own row and pass:
-// a loop step advances each lane by one row of its current pass (the same
-// transport, search and update code for both passes), and a lane that
-// finishes takes the next start from a device queue.  Lanes wait idle
-// until kRefill of them are free (or no lane of the wave works), so that
-// the refill (the tracklet's column of -1 entries and its first state) is
-// issued for several lanes at once.  Per tracklet the arithmetic is the
-// same sequence of operations as build_tracklet's.
-constexpr int kRefill = 8;
-
-enum : int { kLaneIdle = 0, kLaneUp = 1, kLaneDown = 2, kLaneDone = 3, kLaneOut = 4 };
-
-struct LaneTracklet {
-    int64_t t;
-    int32_t* th;          // the tracklet's column: th[r * cap]
-    tpc_sector s;
-    int ph, r, r0, last, miss, nh, rin, h0, hl;
-    int cc, cn, an;       // chain hit of this row, of the next (up); assigned hit below (down)
-    float cy, cz, ay, az, csum;
-    KState st, in;
-    float plast[5];
-};
-
-// start of the down pass from the outermost hit (state at the up pass's
-// last update, position of that hit, initial covariance)
-__device__ __forceinline__ void lane_begin_down(LaneTracklet& L, const tpc_params& prm,
-                                                const float* __restrict__ yg,
-                                                const float* __restrict__ zg, int64_t cap)
-{
-#pragma unroll
-    for (int i = 0; i < 5; ++i) L.st.p[i] = L.plast[i];
-    L.st.p[0] = yg[L.hl];
-    L.st.p[1] = zg[L.hl];
-    reset_cov(L.st, prm);
-    L.in = L.st;
-    L.csum = 0.0f;
-    L.rin = L.last;
-    L.miss = 0;
-    L.an = -1;
-    if (L.last - 1 >= L.r0) {
-        L.an = L.th[(int64_t)(L.last - 1) * cap];
-        if (L.an >= 0) {
-            L.ay = yg[L.an];
-            L.az = zg[L.an];
-        }
-    }
-    L.r = L.last - 1;
-    L.ph = L.r >= 0 ? kLaneDown : kLaneDone;
-}
-
-// first state of tracklet t (its column already holds -1 everywhere)
-__device__ __forceinline__ void lane_init(LaneTracklet& L, int64_t t,
-                                          const tpc_sector* __restrict__ sec, int n_rows,
-                                          const float* xs, const tpc_params& prm,
-                                          const float* __restrict__ yg,
-                                          const float* __restrict__ zg,
-                                          const int32_t* __restrict__ gsr,
-                                          const int32_t* __restrict__ up,
-                                          const int32_t* __restrict__ starts, int64_t cap)
-{
-    const int h0 = starts[t];
-    const int v0 = gsr[h0];
-    L.s = sec[v0 >> 8];
-    L.r0 = v0 & 255;
-    const int h1 = up[h0], h2 = up[h1];
-    const int r2 = gsr[h2] & 255;
-    const float dX = xs[r2] - xs[L.r0];
-    const float T0 = (yg[h2] - yg[h0]) / dX;
-    const float q0 = sqrtf(1.0f + T0 * T0);
-    L.st.p[0] = yg[h0];
-    L.st.p[1] = zg[h0];
-    L.st.p[2] = T0 / q0;
-    L.st.p[3] = (zg[h2] - zg[h0]) / (dX * q0);
-    L.st.p[4] = 0.0f;
-    reset_cov(L.st, prm);
-    L.th[(int64_t)L.r0 * cap] = h0;
-    L.h0 = h0;
-    L.hl = h0;
-    L.last = L.r0;
-    L.nh = 1;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) L.plast[i] = L.st.p[i];
-    L.cc = h1;
-    L.cn = h2;
-    L.cy = yg[h1];
-    L.cz = zg[h1];
-    L.miss = 0;
-    L.r = L.r0 + 1;
-    L.ph = kLaneUp;
-    if (L.r >= n_rows) lane_begin_down(L, prm, yg, zg, cap);
-}
-
-// one row of the lane's current pass
-__device__ __forceinline__ void lane_step(LaneTracklet& L, int n_rows, const float* xs,
-                                          const tpc_params& prm,
-                                          const int32_t* __restrict__ bin_start,
-                                          const float* __restrict__ yg,
-                                          const float* __restrict__ zg,
-                                          const int32_t* __restrict__ idg,
-                                          const int32_t* __restrict__ up, int64_t cap,
-                                          int& n_prop, int& n_upd, int& n_cand)
-{
-    const bool upp = L.ph == kLaneUp;
-    const int r = L.r;
-    int c;
-    float my, mz, ny = 0.0f, nz = 0.0f;
-    int cnn = -1;
-    if (upp) {
-        if (L.cn >= 0) {
-            ny = yg[L.cn];
-            nz = zg[L.cn];
-            cnn = up[L.cn];
-        }
-        c = L.cc;
-        my = L.cy;
-        mz = L.cz;
-    } else {
-        c = L.an;
-        my = L.ay;
-        mz = L.az;
-        L.an = -1;
-        if (r - 1 >= L.r0) {
-            L.an = L.th[(int64_t)(r - 1) * cap];
-            if (L.an >= 0) {
-                L.ay = yg[L.an];
-                L.az = zg[L.an];
-            }
-        }
-    }
-    ++n_prop;
-    const float dx = upp ? xs[r] - xs[r - 1] : xs[r] - xs[r + 1];
-    if (!propagate(L.st, dx, prm.curv, prm.s_max)) {
-        if (upp) {
-            lane_begin_down(L, prm, yg, zg, cap);
-        } else {
-            for (int q = r; q >= 0; --q) {
-                L.nh -= L.th[(int64_t)q * cap] >= 0;
-                L.th[(int64_t)q * cap] = -1;
-            }
-            L.ph = kLaneDone;
-        }
-        return;
-    }
-    const Gain G = gain_of(L.st, prm.sigma_y2, prm.sigma_z2);
-    const bool search = upp ? c < 0 : r < L.r0;
-    if (search) {
-        c = search_row(L.st, G, L.s, r, prm, n_cand, bin_start, yg, zg, idg, my, mz);
-        if (c < 0) {
-            if (++L.miss >= prm.max_miss) {
-                if (upp) lane_begin_down(L, prm, yg, zg, cap);
-                else L.ph = kLaneDone;
-                return;
-            }
-        } else {
-            L.miss = 0;
-        }
-    }
-    if (c >= 0) {
-        ++n_upd;
-        const float chi = kupdate(L.st, G, my, mz);
-        L.th[(int64_t)r * cap] = c;
-        if (upp) {
-            L.last = r;
-            L.hl = c;
-            ++L.nh;
-#pragma unroll
-            for (int i = 0; i < 5; ++i) L.plast[i] = L.st.p[i];
-        } else {
-            L.csum = L.csum + chi;
-            L.rin = r;
-            L.in = L.st;
-            L.nh += r < L.r0;
-        }
-    }
-    if (upp) {
-        if (!search) {
-            L.cc = L.cn;
-            L.cy = ny;
-            L.cz = nz;
-            L.cn = cnn;
-        }
-        L.r = r + 1;
-        if (L.r >= n_rows) lane_begin_down(L, prm, yg, zg, cap);
-    } else {
-        L.r = r - 1;
-        if (L.r < 0) L.ph = kLaneDone;
-    }
-}
-
-// per-wave sum of the work counters into the status block
+// work counters of a wave into the status block: n_prop and n_upd of the
+// wave, n_cand of every lane
 __device__ __forceinline__ void add_work(tpc_status* status, int n_prop, int n_upd, int n_cand)
 {
-    unsigned long long a = n_prop, b = n_upd, c = n_cand;
+    unsigned long long c = n_cand;
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, kWave);
-        b += __shfl_xor(b, o, kWave);
-        c += __shfl_xor(c, o, kWave);
-    }
-    if ((threadIdx.x & (kWave - 1)) == 0 && (a | b | c)) {
-        atomicAdd((unsigned long long*)&status->n_propagations, a);
-        atomicAdd((unsigned long long*)&status->n_updates, b);
+    for (int o = kWave / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0 && (n_prop | n_upd)) {
+        atomicAdd((unsigned long long*)&status->n_propagations, (unsigned long long)n_prop);
+        atomicAdd((unsigned long long*)&status->n_updates, (unsigned long long)n_upd);
         atomicAdd((unsigned long long*)&status->n_candidates, c);
     }
 }
