@@ -526,7 +526,8 @@ typedef struct tpc_track_hits {
  * the last, for tpc_refit_adjoint, in a layout private to the library (tiles
  * of 64 tracks, 20 floats per hit slot; with a checkpoint buffer the tracks
  * are taken in order of decreasing hit count, equal counts in track order,
- * and that order is kept in the buffer too).  A shorter buffer is an
+ * and that order and a copy of the hits by tile are kept in the buffer too:
+ * the adjoint reads the hits there).  A shorter buffer is an
  * argument error, as are n_hits or n_tracks of 2^31 or more.  Outputs do not
  * depend on the order; the adjoint's theta reduction follows it. */
 int tpc_refit(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows, const float* d_row_x,

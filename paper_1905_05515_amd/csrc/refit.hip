@@ -13,8 +13,16 @@
 // symmetric covariance carries a symmetric adjoint G with
 // dL = sum_ij G_ij dC_ij.  Hit gradients are written per hit; the theta
 // gradient is reduced per block in a fixed order, then over blocks.
+//
+// What bounds them: few tracks, the serial chain of one track's hits, at 4.3
+// cycles per VALU instruction (forward 1.3 us a hit, then 0.85; adjoint 2.0,
+// then 1.55, on 400 tracks, with the short division and root sequences and
+// without waits for hits); many, the checkpoints (80 bytes a hit written and
+// read back).
 #include <mutex>
+#include <type_traits>
 
+#include "exact_fp32.hpp"
 #include "tpc_internal.hpp"
 
 namespace tpc {
@@ -37,28 +45,37 @@ inline CalibModel make_calib(const tpc_calib_model& m)
 struct CalHit {
     float x, y, z;      // calibrated plane, y, z
     float xr, yr, dr;   // raw plane x_r, raw y, raw drift length
+    float iv;           // 1 / (x_r tan_half)
     float d, u, v;      // calibrated drift, basis coordinates
 };
 
-__device__ __forceinline__ CalHit calibrate(const float* th, float xr, float yr, float zr, float sd,
-                                            const CalibModel& cm)
+// iv: the reciprocal of the row's xr tan_half.  (The forward functions write
+// their fused multiply-adds out: left to the compiler, the choice of the
+// product that is fused changed with the code around, and a low-momentum
+// track's gradient with it.  kEnd: a hit that starts a pass or ends the
+// reverse sweep, whose drift is rounded once less, as it always was.)
+template <bool kEnd>
+__device__ __forceinline__ CalHit calibrate(const float* th, float xr, float iv, float yr, float zr,
+                                            float sd, const CalibModel& cm)
 {
-#pragma clang fp contract(fast)
     CalHit h;
     h.xr = xr;
+    h.iv = iv;
     h.yr = yr;
-    h.dr = cm.DL - sd * zr;
-    h.d = (1.0f + th[0]) * (h.dr - cm.VD * th[1]);
-    h.z = sd * (cm.DL - h.d);
+    h.dr = fmaf(-sd, zr, cm.DL);
+    const float scale = 1.0f + th[0];
+    const float drift = kEnd ? fmaf(-cm.VD, th[1], h.dr) : h.dr - cm.VD * th[1];
+    h.d = scale * drift;
+    h.z = sd * (kEnd ? fmaf(-scale, drift, cm.DL) : cm.DL - h.d);
     h.u = (xr - cm.UC) * cm.iUS;
-    h.v = yr / (xr * cm.TH);
+    h.v = div_exact(yr, xr * cm.TH, iv);
     const float w = h.d * cm.iDL;
     const float b[7] = {1.0f, h.u, h.v, h.u * h.u, h.u * h.v, h.v * h.v, w};
-    float dr = 0.0f, drphi = 0.0f;
+    float dr = th[2], drphi = th[9];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        dr += th[2 + j] * b[j];
-        drphi += th[9 + j] * b[j];
+    for (int j = 1; j < 7; ++j) {
+        dr = fmaf(th[2 + j], b[j], dr);
+        drphi = fmaf(th[9 + j], b[j], drphi);
     }
     h.x = xr + dr;
     h.y = yr + drphi;
@@ -88,39 +105,27 @@ __device__ __forceinline__ void calibrate_adj(const float* th, const CalHit& h, 
         bb[j] = X * th[2 + j] + Y * th[9 + j];
     }
     const float vb = bb[2] + bb[4] * h.u + 2.0f * bb[5] * h.v;
-    gyr = Y + vb / (h.xr * cm.TH);
+    gyr = Y + div_exact(vb, h.xr * cm.TH, h.iv);
     const float db = bb[6] * cm.iDL - Z * sd;
     gth[0] += (double)(db * (h.dr - cm.VD * th[1]));
     gth[1] += (double)(-db * (1.0f + th[0]) * cm.VD);
     gzr = -sd * (1.0f + th[0]) * db;
 }
 
-// hit i of a track: entry a + i of the CSR, cluster idx[a + i] if given
-struct HitRef {
-    const int32_t* idx;
-    const uint8_t* row_;
-    const float* y_;
-    const float* z_;
-    int a;
-    __device__ __forceinline__ int cl(int i) const { return idx ? idx[a + i] : a + i; }
-    __device__ __forceinline__ int row(int i) const { return row_[cl(i)]; }
-    __device__ __forceinline__ CalHit cal(int i, const float* th, const float* xs, float sd,
-                                          const CalibModel& cm) const
-    {
-        const int c = cl(i);
-        return calibrate(th, xs[row_[c]], y_[c], z_[c], sd, cm);
+// Per pad row: the plane and the reciprocal of plane times tan_half, in LDS.
+__device__ __forceinline__ void load_rows(const float* __restrict__ row_x, int n_rows, float th,
+                                          float2* xs)
+{
+    for (int i = threadIdx.x; i < 256; i += blockDim.x) {
+        const float x = i < n_rows ? row_x[i] : 0.0f;
+        xs[i] = make_float2(x, 1.0f / (x * th));
     }
-    // raw plane, y, z of cluster c (an index from cl)
-    __device__ __forceinline__ void raw(int c, const float* xs, float* r) const
-    {
-        r[0] = xs[row_[c]];
-        r[1] = y_[c];
-        r[2] = z_[c];
-    }
-};
+}
 
 struct Prop {
-    float dx, k, s2, c1, c2, cc, T, q, L, a, a2, g, S, Ts, kdx, Tw, LT, G1, Sk;
+    float dx, k, s2, T, q, L, a, a2, g, S, Ts, kdx, Tw, LT, G1, Sk;
+    float ic1, ic2, icc, iq;        // reciprocals of c1, c2, c1 + c2 and q
+    float e1, e2;                   // s / c1, s2 / c2
     float ys, yw, zs, zt, zw, sw;   // non-trivial Jacobian entries
     float FC[5][5];                 // F C
 };
@@ -130,60 +135,73 @@ struct Prop {
 __device__ __forceinline__ bool prop_fwd(float* p, float* C, float dx, float curv, float s_max,
                                          Prop& P)
 {
-    // the refit is compared with the float64 refit within a tolerance (it
-    // takes no decision but the transport stop), so products and sums may
-    // contract into fused multiply-adds, as in the reverse sweep
-#pragma clang fp contract(fast)
     const float s = p[2], t = p[3], w = p[4];
     P.dx = dx;
     P.k = curv * w;
-    P.s2 = s + P.k * dx;
+    P.s2 = fmaf(P.k, dx, s);
     if (!(fabsf(s) < s_max) || !(fabsf(P.s2) < s_max)) return false;
-    P.c1 = sqrtf((1.0f - s) * (1.0f + s));
-    P.c2 = sqrtf((1.0f - P.s2) * (1.0f + P.s2));
-    P.cc = P.c1 + P.c2;
-    const float icc = 1.0f / P.cc;   // three quotients by c1 + c2
-    P.T = (s + P.s2) * icc;
-    P.q = sqrtf(1.0f + P.T * P.T);
+    const float u1 = (1.0f - s) * (1.0f + s), u2 = (1.0f - P.s2) * (1.0f + P.s2);
+    if (s_max <= 1.0f) {
+        // u >= 2^-24: the short sequences are the correctly rounded operations
+        const float c1 = sqrt_exact(u1), c2 = sqrt_exact(u2);
+        P.icc = rcp_exact(c1 + c2);
+        P.ic1 = rcp_exact(c1);
+        P.ic2 = rcp_exact(c2);
+        P.e1 = div_exact(s, c1, P.ic1);
+        P.e2 = div_exact(P.s2, c2, P.ic2);
+        P.T = (s + P.s2) * P.icc;
+        P.q = sqrt_exact(fmaf(P.T, P.T, 1.0f));
+        P.iq = rcp_exact(P.q);
+    } else {
+        const float c1 = sqrtf(u1), c2 = sqrtf(u2);
+        P.icc = 1.0f / (c1 + c2);
+        P.ic1 = 1.0f / c1;
+        P.ic2 = 1.0f / c2;
+        P.e1 = s / c1;
+        P.e2 = P.s2 / c2;
+        P.T = (s + P.s2) * P.icc;
+        P.q = sqrtf(fmaf(P.T, P.T, 1.0f));
+        P.iq = 1.0f / P.q;
+    }
     P.L = dx * P.q;
     P.a = 0.5f * P.k * P.L;
     P.a2 = P.a * P.a;
-    P.g = 1.0f + P.a2 * ((1.0f / 6.0f) + P.a2 * ((3.0f / 40.0f) + P.a2 * (5.0f / 112.0f)));
+    P.g = fmaf(P.a2, fmaf(P.a2, fmaf(P.a2, 5.0f / 112.0f, 3.0f / 40.0f), 1.0f / 6.0f), 1.0f);
     P.S = P.L * P.g;
-    P.Ts = (2.0f + P.T * (s / P.c1 + P.s2 / P.c2)) * icc;
+    P.Ts = fmaf(P.T, P.e1 + P.e2, 2.0f) * P.icc;
     P.kdx = curv * dx;
-    P.Tw = P.kdx * (1.0f + P.T * (P.s2 / P.c2)) * icc;
-    P.LT = dx * P.T / P.q;
-    P.G1 = 1.0f + P.a2 * (0.5f + P.a2 * ((3.0f / 8.0f) + P.a2 * (5.0f / 16.0f)));
-    P.Sk = P.L * P.L * P.a * ((1.0f / 6.0f) + P.a2 * ((3.0f / 20.0f) + P.a2 * (15.0f / 112.0f)));
+    P.Tw = P.kdx * fmaf(P.T, P.e2, 1.0f) * P.icc;
+    P.LT = div_exact(dx * P.T, P.q, P.iq);
+    P.G1 = fmaf(P.a2, fmaf(P.a2, fmaf(P.a2, 5.0f / 16.0f, 3.0f / 8.0f), 0.5f), 1.0f);
+    P.Sk = P.L * P.L * P.a * fmaf(P.a2, fmaf(P.a2, 15.0f / 112.0f, 3.0f / 20.0f), 1.0f / 6.0f);
     P.ys = dx * P.Ts;
     P.yw = dx * P.Tw;
     const float m1 = P.G1 * P.LT;
     P.zs = t * m1 * P.Ts;
     P.zt = P.S;
-    P.zw = t * (m1 * P.Tw + P.Sk * curv);
+    P.zw = t * fmaf(P.Sk, curv, m1 * P.Tw);
     P.sw = P.kdx;
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         const float cy = C[lt(0, j)], cz = C[lt(1, j)], cs = C[lt(2, j)];
         const float ct = C[lt(3, j)], cw = C[lt(4, j)];
-        P.FC[0][j] = cy + P.ys * cs + P.yw * cw;
-        P.FC[1][j] = cz + P.zs * cs + P.zt * ct + P.zw * cw;
-        P.FC[2][j] = cs + P.sw * cw;
+        P.FC[0][j] = fmaf(P.yw, cw, fmaf(P.ys, cs, cy));
+        P.FC[1][j] = fmaf(P.zw, cw, fmaf(P.zt, ct, fmaf(P.zs, cs, cz)));
+        P.FC[2][j] = fmaf(P.sw, cw, cs);
         P.FC[3][j] = ct;
         P.FC[4][j] = cw;
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         const float* B = P.FC[i];
-        C[lt(i, 0)] = B[0] + P.ys * B[2] + P.yw * B[4];
-        if (i >= 1) C[lt(i, 1)] = B[1] + P.zs * B[2] + P.zt * B[3] + P.zw * B[4];
-        if (i >= 2) C[lt(i, 2)] = B[2] + P.sw * B[4];
+        C[lt(i, 0)] = fmaf(P.yw, B[4], fmaf(P.ys, B[2], B[0]));
+        if (i >= 1) C[lt(i, 1)] = fmaf(P.zw, B[4], fmaf(P.zt, B[3], fmaf(P.zs, B[2], B[1])));
+        if (i >= 2) C[lt(i, 2)] = fmaf(P.sw, B[4], B[2]);
         if (i >= 3) C[lt(i, 3)] = B[3];
         if (i >= 4) C[lt(i, 4)] = B[4];
     }
-    p[0] = p[0] + dx * P.T;
-    p[1] = p[1] + t * P.S;
+    p[0] = fmaf(dx, P.T, p[0]);
+    p[1] = fmaf(t, P.S, p[1]);
     p[2] = P.s2;
     return true;
 }
@@ -196,15 +214,15 @@ struct Upd {
 __device__ __forceinline__ float upd_fwd(float* p, float* C, float my, float mz, float sy2,
                                          float sz2, Upd& U)
 {
-#pragma clang fp contract(fast)
     U.r0 = my - p[0];
     U.r1 = mz - p[1];
     const float S00 = C[0] + sy2, S10 = C[1], S11 = C[2] + sz2;
-    const float idet = 1.0f / (S00 * S11 - S10 * S10);
+    const float idet = rcp_any(fmaf(S00, S11, -(S10 * S10)));
     U.B00 = S11 * idet;
     U.B10 = -S10 * idet;
     U.B11 = S00 * idet;
-    const float chi2 = U.r0 * (U.B00 * U.r0 + U.B10 * U.r1) + U.r1 * (U.B10 * U.r0 + U.B11 * U.r1);
+    const float chi2 = fmaf(U.r0, fmaf(U.B00, U.r0, U.B10 * U.r1),
+                            U.r1 * fmaf(U.B10, U.r0, U.B11 * U.r1));
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         U.A0[i] = C[lt(i, 0)];
@@ -212,14 +230,16 @@ __device__ __forceinline__ float upd_fwd(float* p, float* C, float my, float mz,
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-        U.K0[i] = U.A0[i] * U.B00 + U.A1[i] * U.B10;
-        U.K1[i] = U.A0[i] * U.B10 + U.A1[i] * U.B11;
+        U.K0[i] = fmaf(U.A0[i], U.B00, U.A1[i] * U.B10);
+        U.K1[i] = i == 1 ? fmaf(U.A1[i], U.B11, U.A0[i] * U.B10)
+                         : fmaf(U.A0[i], U.B10, U.A1[i] * U.B11);
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
-        p[i] += U.K0[i] * U.r0 + U.K1[i] * U.r1;
+        p[i] += fmaf(U.K0[i], U.r0, U.K1[i] * U.r1);
 #pragma unroll
-        for (int j = 0; j <= i; ++j) C[lt(i, j)] -= U.K0[i] * U.A0[j] + U.K1[i] * U.A1[j];
+        for (int j = 0; j <= i; ++j)
+            C[lt(i, j)] -= fmaf(U.K0[i], U.A0[j], U.K1[i] * U.A1[j]);
     }
     return chi2;
 }
@@ -368,10 +388,7 @@ __device__ __forceinline__ float prop_adj(const Prop& P, const float* p0, const 
     float a2b = Skb * P.L * P.L * P.a * hp;
     // G1 = 1 + a2 (1/2 + a2 (3/8 + a2 5/16))
     a2b += G1b * (0.5f + P.a2 * (2.0f * (3.0f / 8.0f) + P.a2 * (3.0f * (5.0f / 16.0f))));
-    // the reverse sweep divides by four quantities only: their reciprocals
-    // once (the gradient is compared within a tolerance, not bit for bit,
-    // and a correctly rounded division costs a dozen instructions)
-    const float iq = 1.0f / P.q, icc = 1.0f / P.cc, ic1 = 1.0f / P.c1, ic2 = 1.0f / P.c2;
+    const float iq = P.iq, icc = P.icc, ic1 = P.ic1, ic2 = P.ic2;
     // LT = dx T / q
     dxb += LTb * P.T * iq;
     Tb += LTb * P.dx * iq;
@@ -482,45 +499,128 @@ __device__ __forceinline__ void load_theta(const float* __restrict__ d_theta, fl
     __syncthreads();
 }
 
-// ---- staging of a wave's hits through LDS ---------------------------------
-// The 64 tracks of a wave are consecutive in the CSR, so hits [i0, i0 + K)
-// of all of them are 64 short contiguous runs.  The wave loads them
-// cooperatively (item e of a chunk: track e / K, hit i0 + e % K), K runs of
-// K hits per load instruction instead of 64 scattered words, and each lane
-// then reads its own hits from LDS.  Gradients leave the same way.
-constexpr int kChunk = 8;
+// ---- the hits of a lane's track, without checkpoints ----------------------
+// A lane reads its track's hits kChunk at a time, as vector loads (its run
+// of the CSR is contiguous, at any alignment of 4 bytes), a chunk ahead of
+// their use, and puts them into its own column of LDS when their chunk
+// begins.  The chunk at slot i0 of a track of n hits holds the hits [base,
+// base + kChunk), base = min(i0, n - kChunk), so that the last one reads no
+// entry past the track.  (Loading them cooperatively, as runs of 8 hits of
+// 8 tracks per instruction, and waiting for each instruction's hits took 9000
+// cycles per 8 hits, half of the forward kernel's time on 400 tracks.)
+constexpr int kChunk = 4;
 
-struct Stage {
-    float x[kChunk][kWave];   // raw plane position of the hit's row
-    float y[kChunk][kWave];
-    float z[kChunk][kWave];
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t int4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uint32_u __attribute__((aligned(1)));
+
+struct HitRows {
+    const int32_t* __restrict__ idx;
+    const uint8_t* __restrict__ row;
+    const float* __restrict__ y;
+    const float* __restrict__ z;
+    const int32_t* __restrict__ off;
 };
 
-// stage hits [i0, i0 + kChunk) of the wave's tracks (a, n of each lane);
-// flags a hit row >= n_rows in bad[lane of the track]
-__device__ __forceinline__ void stage_hits(Stage& S, int* bad, int i0, int a, int n,
-                                           const int32_t* __restrict__ idx,
-                                           const uint8_t* __restrict__ row,
-                                           const float* __restrict__ y,
-                                           const float* __restrict__ z, const float* xs,
-                                           int n_rows)
+struct HitChunk {
+    float4_u y, z;
+    uint32_t row;      // a byte per hit
+    int base;
+    int4_u c;          // with an index: clusters of the chunk to load next
+};
+
+// first hit of the chunk at slot i0 of a track of n hits
+__device__ __forceinline__ int chunk_base(int i0, int n)
 {
-    const int lane = threadIdx.x & (kWave - 1);
+    const int b = i0 < n - kChunk ? i0 : n - kChunk;
+    return b > 0 ? b : 0;
+}
+
+// the cluster indices of the chunk at slot i0 of the track at entry a (n
+// hits; three hits: the third stands for a fourth)
+__device__ __forceinline__ void load_index(HitChunk& h, const HitRows& in, int a, int n, int i0)
+{
+    if (n >= kChunk) {
+        h.c = *reinterpret_cast<const int4_u*>(in.idx + a + chunk_base(i0, n));
+    } else {
 #pragma unroll
-    for (int j = 0; j < kChunk; ++j) {
-        const int e = lane + kWave * j;
-        const int l = e / kChunk, k = e % kChunk;
-        const int al = __shfl(a, l, kWave), nl = __shfl(n, l, kWave);
-        const int i = i0 + k;
-        if (i < nl) {
-            const int c = idx ? idx[al + i] : al + i;
-            const int r = row[c];
-            if (r >= n_rows) bad[l] = 1;
-            S.x[k][l] = xs[r];
-            S.y[k][l] = y[c];
-            S.z[k][l] = z[c];
-        }
+        for (int k = 0; k < kChunk; ++k) h.c[k] = in.idx[a + (k < n ? k : n - 1)];
     }
+}
+
+// load the chunk at slot i0; with an index (kIdx) its clusters, whose
+// indices load_index has loaded a chunk earlier (two loads in a row, each
+// waiting for the last, would stand in every chunk's way)
+template <bool kIdx>
+__device__ __forceinline__ void load_chunk(HitChunk& h, const HitRows& in, int a, int n, int i0)
+{
+    h.base = chunk_base(i0, n);
+    const int e = a + h.base;
+    if (!kIdx && n >= kChunk) {
+        h.y = *reinterpret_cast<const float4_u*>(in.y + e);
+        h.z = *reinterpret_cast<const float4_u*>(in.z + e);
+        h.row = *reinterpret_cast<const uint32_u*>(in.row + e);
+        return;
+    }
+    uint32_t r[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+        const int c = kIdx ? h.c[k] : a + (k < n ? k : n - 1);
+        h.y[k] = in.y[c];
+        h.z[k] = in.z[c];
+        r[k] = in.row[c];
+    }
+    h.row = r[0] | r[1] << 8 | r[2] << 16 | r[3] << 24;
+}
+
+// the chunk into the lane's LDS column (plane, y, z, reciprocal of plane
+// times tan_half per hit); true if a hit's row is outside the table
+__device__ __forceinline__ bool put_chunk(const HitChunk& h, float4* col, const float2* xs,
+                                          int n_rows)
+{
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+        const int r = (int)(h.row >> (8 * k)) & 255;
+        bad |= r >= n_rows;
+        const float2 x = xs[r];
+        col[k * kWave] = make_float4(x.x, h.y[k], h.z[k], x.y);
+    }
+    return bad;
+}
+
+// ---- packed hits, with checkpoints ------------------------------------------
+// The checkpoint buffer also holds the hits of the tile's tracks by (slot,
+// lane): the forward pass and the adjoint read each slot as whole lines.
+// (Read from the CSR a few hits at a time, the 64 tracks of each wave in
+// flight keep more lines open than the L2s hold, and every visit fetched its
+// line again: 5.5 GB for the 0.86 GB of a million tracks, in each kernel.)
+struct PackedHits {
+    float2* yz;        // [tile][n_rows][64]
+    uint8_t* row;      // [tile][n_rows][64]
+    uint8_t* bad;      // [tile][part][64]: a hit's row is outside the table
+};
+
+// one lane's hits of a tile
+struct PackedCol {
+    const float2* yz;
+    const uint8_t* row;
+};
+
+__device__ __forceinline__ PackedCol packed_col(const PackedHits& h, int64_t q, int n_rows)
+{
+    const int64_t o = (q / kWave) * (int64_t)n_rows * kWave + (q & (kWave - 1));
+    return {h.yz + o, h.row + o};
+}
+
+struct RawHit {
+    float2 yz;
+    int row;
+};
+
+__device__ __forceinline__ RawHit raw_at(const PackedCol& c, int i)
+{
+    return {c.yz[i * kWave], c.row[i * kWave]};
 }
 
 }  // namespace
@@ -614,98 +714,223 @@ __device__ __forceinline__ int64_t track_at(const int32_t* __restrict__ order, i
     return order && q < nt ? (int64_t)order[q] : q;
 }
 
+// The hits of 64 tracks (consecutive in the tile order) into their tile, one
+// block per (tile, kPackSlots slots; the last block of a tile also looks at
+// the hits past the rows): a wave reads kPackRuns tracks' runs at a time,
+// 64 entries of each, into LDS, and the block writes the tile slot by slot.
+// Streaming: 1M tracks' hits, 0.86 GB read and written.
+constexpr int kPackSlots = kWave;
+constexpr int kPackRuns = 8;
+
+__host__ __device__ inline int pack_parts(int n_rows)
+{
+    return (n_rows + kPackSlots - 1) / kPackSlots;
+}
+
+__global__ __launch_bounds__(kBlock) void k_refit_pack(
+    HitRows in, const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows,
+    const int32_t* __restrict__ order, PackedHits out)
+{
+    __shared__ float2 yz[kPackSlots][kWave + 1];
+    __shared__ uint8_t rw[kPackSlots][kWave + 4];
+    __shared__ int a_[kWave], n_[kWave], bad[kWave], longest;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    constexpr int kWaves = kBlock / kWave;
+    const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
+    const int parts = pack_parts(n_rows);
+    const int64_t units = (nt + kWave - 1) / kWave * parts;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const int64_t tb = u / parts * kWave;
+        const int part = (int)(u % parts);
+        if (threadIdx.x < kWave) {
+            const int64_t t = track_at(order, tb + lane, nt);
+            int a = 0, n = 0;
+            if (t < nt) {
+                a = in.off[t];
+                n = in.off[t + 1] - a;
+            }
+            n = n >= 3 ? n : 0;
+            a_[lane] = a;
+            n_[lane] = n;
+            bad[lane] = 0;
+            const int m = wave_max(n);
+            if (lane == 0) longest = m;
+        }
+        __syncthreads();
+        const int first = part * kPackSlots;
+        const int past = part + 1 < parts ? first + kPackSlots : longest;
+        for (int i0 = first; i0 < longest && i0 < past; i0 += kPackSlots) {
+            const int i = i0 + lane;
+            for (int l0 = wid; l0 < kWave; l0 += kWaves * kPackRuns) {
+                int c[kPackRuns];
+                float y[kPackRuns], z[kPackRuns];
+                uint8_t r[kPackRuns];
+#pragma unroll
+                for (int k = 0; k < kPackRuns; ++k) {
+                    const int l = l0 + k * kWaves;
+                    c[k] = -1;
+                    if (i < n_[l]) c[k] = in.idx ? in.idx[a_[l] + i] : a_[l] + i;
+                }
+#pragma unroll
+                for (int k = 0; k < kPackRuns; ++k)
+                    if (c[k] >= 0) {
+                        y[k] = in.y[c[k]];
+                        z[k] = in.z[c[k]];
+                        r[k] = in.row[c[k]];
+                    }
+#pragma unroll
+                for (int k = 0; k < kPackRuns; ++k)
+                    if (c[k] >= 0) {
+                        const int l = l0 + k * kWaves;
+                        yz[lane][l] = make_float2(y[k], z[k]);
+                        rw[lane][l] = r[k];
+                        if (r[k] >= n_rows) bad[l] = 1;
+                    }
+            }
+            __syncthreads();
+            const int n = n_[lane];
+            for (int k = wid; k < kPackSlots && i0 + k < n_rows && i0 + k < longest; k += kWaves)
+                if (i0 + k < n) {
+                    const int64_t o = (u / parts * n_rows + i0 + k) * kWave + lane;
+                    out.yz[o] = yz[k][lane];
+                    out.row[o] = rw[k][lane];
+                }
+            __syncthreads();
+        }
+        if (threadIdx.x < kWave) out.bad[(u / parts * parts + part) * kWave + lane] = (uint8_t)bad[lane];
+        __syncthreads();
+    }
+}
+
+constexpr std::true_type kYes{};
+constexpr std::false_type kNo{};
+
+// where the forward pass reads its hits
+enum { kCsr = 0, kCsrIndex = 1, kPacked = 2 };
+
+template <int kFrom>
 __global__ __launch_bounds__(kWave) void k_refit_fwd(
-    const int32_t* __restrict__ off, const int32_t* __restrict__ idx,
-    const uint8_t* __restrict__ row, const float* __restrict__ y, const float* __restrict__ z,
-    const int8_t* __restrict__ side, const int64_t* __restrict__ d_count, int64_t n_tracks,
-    int n_rows,
-    const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
+    HitRows in, PackedHits packed, const int8_t* __restrict__ side, const int64_t* __restrict__ d_count,
+    int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
     const float* __restrict__ d_theta, float* __restrict__ par, float* __restrict__ cov,
     float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck,
     const int32_t* __restrict__ order)
 {
     __shared__ float th[16];
-    __shared__ float xs[256];
-    __shared__ Stage S;
-    __shared__ int bad[kWave];
+    __shared__ float2 xs[256];
+    __shared__ float4 hits[kFrom == kPacked ? kWave : kChunk * kWave];
+    constexpr bool kIdx = kFrom == kCsrIndex;
     load_theta(d_theta, th);
-    for (int i = threadIdx.x; i < n_rows; i += blockDim.x) xs[i] = row_x[i];
+    load_rows(row_x, n_rows, cm.TH, xs);
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
+    float4* col = hits + lane;
     const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
     // one wave per tile of 64 tracks (consecutive in the tile order)
     for (int64_t tb = blockIdx.x * (int64_t)kWave; tb < nt; tb += (int64_t)gridDim.x * kWave) {
         const int64_t t = track_at(order, tb + lane, nt);
         int a = 0, n = 0;
         if (t < nt) {
-            a = off[t];
-            n = off[t + 1] - a;
+            a = in.off[t];
+            n = in.off[t + 1] - a;
         }
         // tracks filtered: at least 3 hits, not more hits than rows (a hit
         // row outside the table is found while staging)
-        const bool fit = t < nt && n >= 3 && n <= n_rows;
-        const int M = wave_max(t < nt && n >= 3 ? n : 0);
-        bad[lane] = 0;
+        const int ns = n >= 3 ? n : 0;
+        const bool fit = n >= 3 && n <= n_rows;
+        const int M = wave_max(ns);
         float p[5] = {0, 0, 0, 0, 0}, C[15];
 #pragma unroll
         for (int i = 0; i < 15; ++i) C[i] = 0.0f;
         float chi2 = 0.0f, xp = 0.0f;
-        bool alive = fit;
+        bool alive = fit, bad = false;
         int stat = 0;
         const float sd = t < nt && side ? (float)side[t] : 1.0f;
         // every lane of a tile stores every slot up to the wave's longest
         // track (a lane past its own track stores its unchanged state, which
         // nothing reads), so that each store writes whole lines; the tile of
         // the last, partial wave is allocated in full
-        float4* ckt = ck ? ck_tile(ck, tb + lane, n_rows) : nullptr;
+        float4* ckt = kFrom == kPacked ? ck_tile(ck, tb + lane, n_rows) : nullptr;
         const int M_ck = M < n_rows ? M : n_rows;
-        for (int i0 = 0; i0 < M; i0 += kChunk) {
-            __syncthreads();      // the previous chunk is consumed
-            stage_hits(S, bad, i0, a, t < nt && n >= 3 ? n : 0, idx, row, y, z, xs, n_rows);
-            __syncthreads();
-            if (i0 == 0 && alive) {
-                // state from the first and third hits
-                const CalHit h0 = calibrate(th, S.x[0][lane], S.y[0][lane], S.z[0][lane], sd, cm);
-                const CalHit h2 = calibrate(th, S.x[2][lane], S.y[2][lane], S.z[2][lane], sd, cm);
-                const float dX = h2.x - h0.x;
-                const float T0 = (h2.y - h0.y) / dX;
-                const float q0 = sqrtf(1.0f + T0 * T0);
-                p[0] = h0.y;
-                p[1] = h0.z;
-                p[2] = T0 / q0;
-                p[3] = (h2.z - h0.z) / (dX * q0);
-                p[4] = 0.0f;
-                C[0] = prm.sigma_y2;
-                C[2] = prm.sigma_z2;
-                C[5] = prm.c_ss0;
-                C[9] = prm.c_tt0;
-                C[14] = prm.c_ww0;
-                xp = h0.x;
+        auto start = [&](const CalHit& h0, const CalHit& h2) {
+            // state from the first and third hits
+            const float dX = h2.x - h0.x;
+            const float T0 = (h2.y - h0.y) / dX;
+            const float q0 = sqrtf(1.0f + T0 * T0);
+            p[0] = h0.y;
+            p[1] = h0.z;
+            p[2] = T0 / q0;
+            p[3] = (h2.z - h0.z) / (dX * q0);
+            p[4] = 0.0f;
+            C[0] = prm.sigma_y2;
+            C[2] = prm.sigma_z2;
+            C[5] = prm.c_ss0;
+            C[9] = prm.c_tt0;
+            C[14] = prm.c_ww0;
+            xp = h0.x;
+        };
+        auto step = [&](const CalHit& h) {
+            Prop P;
+            if (prop_fwd(p, C, h.x - xp, prm.curv, prm.s_max, P)) {
+                Upd U;
+                chi2 += upd_fwd(p, C, h.y, h.z, prm.sigma_y2, prm.sigma_z2, U);
+                xp = h.x;
+            } else {
+                stat = 2;
+                alive = false;
             }
-            if (i0 == 0 && ckt && M_ck > 1) store_ck(ckt, 0, p, C);
-            const int i_hi = i0 + kChunk < M ? i0 + kChunk : M;
-            for (int i = i0 > 1 ? i0 : 1; i < i_hi; ++i) {
-                if (alive && i < n) {
-                    const int k = i - i0;
-                    const CalHit h =
-                        calibrate(th, S.x[k][lane], S.y[k][lane], S.z[k][lane], sd, cm);
-                    Prop P;
-                    if (prop_fwd(p, C, h.x - xp, prm.curv, prm.s_max, P)) {
-                        Upd U;
-                        chi2 += upd_fwd(p, C, h.y, h.z, prm.sigma_y2, prm.sigma_z2, U);
-                        xp = h.x;
-                    } else {
-                        stat = 2;
-                        alive = false;
-                    }
+        };
+        if (kFrom == kPacked) {
+            const PackedCol hp = packed_col(packed, tb + lane, n_rows);
+            auto cal = [&](const RawHit& r, auto end) {
+                const float2 x = xs[r.row];
+                return calibrate<end()>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
+            };
+            // hits of the next two slots, in flight
+            RawHit r1{}, r2{};
+            if (alive) {
+                r1 = raw_at(hp, 1);
+                r2 = raw_at(hp, 2);
+                start(cal(raw_at(hp, 0), kYes), cal(r2, kYes));
+            }
+            if (M_ck > 1) store_ck(ckt, 0, p, C);
+            for (int i = 1; i < M_ck; ++i) {
+                const RawHit r = r1;
+                r1 = r2;
+                if (alive && i + 2 < n) r2 = raw_at(hp, i + 2);
+                if (alive && i < n) step(cal(r, kNo));
+                if (i + 1 < M_ck) store_ck(ckt, i, p, C);
+            }
+            const int parts = pack_parts(n_rows);
+            for (int k = 0; k < parts; ++k)
+                bad |= packed.bad[(tb / kWave * parts + k) * kWave + lane] != 0;
+        } else {
+            HitChunk nx{};
+            if (ns > 0) {
+                if (kIdx) load_index(nx, in, a, n, 0);
+                load_chunk<kIdx>(nx, in, a, n, 0);
+                if (kIdx) load_index(nx, in, a, n, kChunk);
+            }
+            for (int i0 = 0; i0 < M; i0 += kChunk) {
+                const int base = nx.base;
+                if (i0 < ns) bad |= put_chunk(nx, col, xs, n_rows);
+                if (i0 + kChunk < ns) {
+                    load_chunk<kIdx>(nx, in, a, n, i0 + kChunk);
+                    if (kIdx) load_index(nx, in, a, n, i0 + 2 * kChunk);
                 }
-                if (ckt && i + 1 < M_ck) store_ck(ckt, i, p, C);
+                auto cal = [&](int k, auto end) {
+                    const float4 r = col[k * kWave];
+                    return calibrate<end()>(th, r.x, r.w, r.y, r.z, sd, cm);
+                };
+                if (i0 == 0 && alive) start(cal(0, kYes), cal(2, kYes));
+                const int i_hi = i0 + kChunk < M ? i0 + kChunk : M;
+                for (int i = i0 > 1 ? i0 : 1; i < i_hi; ++i)
+                    if (alive && i < n) step(cal(i - base, kNo));
             }
         }
-        __syncthreads();
         if (t < nt) {
             if (n < 3) stat = 1;
-            else if (bad[lane]) stat = 3;
+            else if (bad) stat = 3;
             else if (n > n_rows) stat = 4;
             if (stat == 1 || stat == 3 || stat == 4) {
                 chi2 = 0.0f;
@@ -724,12 +949,14 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
     }
 }
 
-__global__ __launch_bounds__(kWave) void k_refit_adj(
-    const int32_t* __restrict__ off, const int32_t* __restrict__ idx,
-    const uint8_t* __restrict__ row, const float* __restrict__ y, const float* __restrict__ z,
-    const int8_t* __restrict__ side, const int64_t* __restrict__ d_count, int64_t n_tracks,
-    int n_rows,
-    const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
+// Hit gradients of kGrads slots leave together: 16 lanes write 16 entries of
+// one track, so that most of a line is written by one instruction.
+constexpr int kGrads = 16;
+
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
+void k_refit_adj(
+    const int32_t* __restrict__ off, PackedHits packed, const int8_t* __restrict__ side,
+    const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
     const float* __restrict__ d_theta, const float* __restrict__ ck,
     const int32_t* __restrict__ status, const float* __restrict__ gchi2,
     const float* __restrict__ seed_p, const float* __restrict__ seed_x,
@@ -737,12 +964,11 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
     const int32_t* __restrict__ order)
 {
     __shared__ float th[16];
-    __shared__ float xs[256];
-    __shared__ Stage S;
-    __shared__ float Gy[kChunk][kWave], Gz[kChunk][kWave];
-    __shared__ int bad[kWave];
+    __shared__ float2 xs[256];
+    // the hit gradients of kGrads slots, y then z, by lane
+    __shared__ float grads[2][kWave][kGrads + 1];
     load_theta(d_theta, th);
-    for (int i = threadIdx.x; i < n_rows; i += blockDim.x) xs[i] = row_x[i];
+    load_rows(row_x, n_rows, cm.TH, xs);
     __syncthreads();
     double gth[16];
 #pragma unroll
@@ -751,8 +977,7 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
     const int lane = threadIdx.x & (kWave - 1);
     // one wave per tile of 64 tracks; the reverse sweep runs over the slots
     // of the tile in lockstep (slot i is active in the lanes whose track has
-    // more than i hits), so that checkpoint loads are whole lines; hits come
-    // through LDS in chunks, from the top down
+    // more than i hits), so that hit and checkpoint loads are whole lines
     for (int64_t tb = blockIdx.x * (int64_t)kWave; tb < nt; tb += (int64_t)gridDim.x * kWave) {
         const int64_t t = track_at(order, tb + lane, nt);
         int a = 0, n = 0;
@@ -769,7 +994,7 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
         const int ne = fit ? n : 0;
         const int M = wave_max(ne);
         if (M == 0) continue;
-        HitRef H{idx, row, y, z, a};
+        const PackedCol hp = packed_col(packed, tb + lane, n_rows);
         const float4* ckt = ck_tile(const_cast<float*>(ck), tb + lane, n_rows);
         const float sd = fit && side ? (float)side[t] : 1.0f;
         const float cb = fit ? gchi2[t] : 0.0f;
@@ -781,26 +1006,29 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
             for (int i = 0; i < 5; ++i) pb[i] = seed_p[t * 5 + i];
 #pragma unroll
         for (int i = 0; i < 15; ++i) G[i] = 0.0f;
+        auto cal = [&](const RawHit& r, auto end) {
+            const float2 x = xs[r.row];
+            return calibrate<end()>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
+        };
         CalHit cur{};
+        RawHit r1{};       // hit of the coming slot, loaded a step ahead
         // checkpoint of the coming step (slot i - 1), loaded a step ahead
         float4 ck4[5];
         if (fit) {
-            cur = H.cal(n - 1, th, xs, sd, cm);
+            cur = cal(raw_at(hp, n - 1), kYes);
+            r1 = raw_at(hp, n - 2);
             load_ck(ckt, n - 2, ck4);
         }
         // dL/dx of the last hit's calibrated plane from the caller's terms
         float Xcarry = fit && seed_x ? seed_x[t] : 0.0f;
         float X2 = 0.0f, Y2 = 0.0f, Z2 = 0.0f;
-        // steps i = top .. lo need hits lo - 1 .. top - 1 (the previous hit)
+        // step i needs hit i - 1; the gradients leave kGrads slots at a time
         for (int top = M - 1; top >= 1;) {
-            const int lo = top - kChunk + 1 > 1 ? top - kChunk + 1 : 1;
-            __syncthreads();
-            stage_hits(S, bad, lo - 1, a, ne, idx, row, y, z, xs, n_rows);
-            __syncthreads();
+            const int lo = top / kGrads * kGrads > 1 ? top / kGrads * kGrads : 1;
             for (int i = top; i >= lo; --i) {
                 if (i >= ne) continue;
-                const int k = i - lo;             // slot of hit i - 1
-                const CalHit prev = calibrate(th, S.x[k][lane], S.y[k][lane], S.z[k][lane], sd, cm);
+                const CalHit prev = cal(r1, kNo);
+                if (i >= 2) r1 = raw_at(hp, i - 2);
                 float p[5], C[15];
                 unpack_ck(ck4, p, C);
                 if (i >= 2) load_ck(ckt, i - 2, ck4);
@@ -820,24 +1048,19 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
                 } else {
                     float gyr, gzr;
                     calibrate_adj(th, cur, sd, cm, Xi, myb, mzb, gth, gyr, gzr);
-                    Gy[i - lo][lane] = gyr;
-                    Gz[i - lo][lane] = gzr;
+                    grads[0][lane][i - lo] = gyr;
+                    grads[1][lane][i - lo] = gzr;
                 }
                 Xcarry = -dxb;
                 cur = prev;
             }
-            __syncthreads();
-            // write the chunk's hit gradients (hits lo .. top, but hit 2),
-            // the same runs as the staging
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                const int e = lane + kWave * j;
-                const int l = e / kChunk, kk = e % kChunk;
+            // hits lo .. top, but hit 2: kGrads lanes write one track's run
+            const int i = lo + (lane & (kGrads - 1));
+            for (int l = lane / kGrads; l < kWave; l += kWave / kGrads) {
                 const int al = __shfl(a, l, kWave), nl = __shfl(ne, l, kWave);
-                const int i = lo + kk;
                 if (i <= top && i < nl && i != 2) {
-                    gy[al + i] = Gy[kk][l];
-                    gz[al + i] = Gz[kk][l];
+                    gy[al + i] = grads[0][l][i - lo];
+                    gz[al + i] = grads[1][l][i - lo];
                 }
             }
             top = lo - 1;
@@ -845,7 +1068,7 @@ __global__ __launch_bounds__(kWave) void k_refit_adj(
         if (!fit) continue;
         // initial state: y, z of hit 0, direction from hit 0 to hit 2
         const CalHit h0 = cur;
-        const CalHit h2 = H.cal(2, th, xs, sd, cm);
+        const CalHit h2 = cal(raw_at(hp, 2), kYes);
         const float dX = h2.x - h0.x;
         const float T0 = (h2.y - h0.y) / dX;
         const float q0 = sqrtf(1.0f + T0 * T0);
@@ -933,10 +1156,10 @@ __global__ __launch_bounds__(kBlock) void k_vertex_residual(
         float l = 0.0f, gx = 0.0f, gp[5] = {0, 0, 0, 0, 0}, w[3] = {0, 0, 0};
         bool good = status[t] == 0 && n >= 3;
         if (good) {
-            const HitRef H{idx, row, y, z, a};
-            const int c = H.cl(n - 1);
+            const int c = idx ? idx[a + n - 1] : a + n - 1;
             const float sd = side ? (float)side[t] : 1.0f;
-            const float xl = calibrate(th, row_x[row[c]], y[c], z[c], sd, cm).x;
+            const float xr = row_x[row[c]];
+            const float xl = calibrate<true>(th, xr, 1.0f / (xr * cm.TH), y[c], z[c], sd, cm).x;
             float p[5], C[15];
 #pragma unroll
             for (int i = 0; i < 5; ++i) p[i] = par[t * 5 + i];
@@ -1006,9 +1229,10 @@ static unsigned refit_grid(int64_t n_tracks)
 }
 
 // The checkpoint buffer: the tiles, then the tile order (int32 per track),
-// the per-(key, block) counts of the ordering and its scan partials.
+// the per-(key, block) counts of the ordering, its scan partials and the
+// packed hits.
 struct CkLayout {
-    size_t order_off, cnt_off, part_off, total;
+    size_t order_off, cnt_off, part_off, yz_off, row_off, bad_off, total;
     int64_t nblk;
     int nkeys;
 };
@@ -1025,7 +1249,11 @@ static CkLayout ck_layout(int64_t n_tracks, int n_rows)
     L.order_off = ck_align(sizeof(float) * (size_t)tiles * kWave * (size_t)n_rows * 20);
     L.cnt_off = L.order_off + ck_align(sizeof(int32_t) * (size_t)(n_tracks > 0 ? n_tracks : 1));
     L.part_off = L.cnt_off + ck_align(sizeof(int32_t) * (size_t)ncnt);
-    L.total = L.part_off + sizeof(int64_t) * (size_t)(ceil_div(ncnt, kScanTile) + 1);
+    L.yz_off = L.part_off + ck_align(sizeof(int64_t) * (size_t)(ceil_div(ncnt, kScanTile) + 1));
+    const size_t slots = (size_t)tiles * kWave * (size_t)n_rows;
+    L.row_off = L.yz_off + ck_align(sizeof(float2) * slots);
+    L.bad_off = L.row_off + ck_align(slots);
+    L.total = L.bad_off + (size_t)tiles * kWave * (size_t)pack_parts(n_rows);
     return L;
 }
 
@@ -1035,7 +1263,16 @@ static const int32_t* ck_order(const float* ck, int64_t n_tracks, int n_rows)
                                             ck_layout(n_tracks, n_rows).order_off);
 }
 
-// the tile order of the forward pass, into the checkpoint buffer
+static PackedHits ck_packed(const float* ck, int64_t n_tracks, int n_rows)
+{
+    const CkLayout L = ck_layout(n_tracks, n_rows);
+    char* b = reinterpret_cast<char*>(const_cast<float*>(ck));
+    return {reinterpret_cast<float2*>(b + L.yz_off), reinterpret_cast<uint8_t*>(b + L.row_off),
+            reinterpret_cast<uint8_t*>(b + L.bad_off)};
+}
+
+// the tile order of the forward pass and the packed hits, into the
+// checkpoint buffer
 static void launch_order(const tpc_track_hits& hits, int n_rows, float* ck, hipStream_t st)
 {
     const CkLayout L = ck_layout(hits.n_tracks, n_rows);
@@ -1048,6 +1285,11 @@ static void launch_order(const tpc_track_hits& hits, int n_rows, float* ck, hipS
     launch_scan<int32_t>(cnt, cnt, L.nblk * L.nkeys, false, nullptr, nullptr, part, st);
     TPC_LAUNCH(k_order_place, dim3((unsigned)L.nblk), dim3(kOrdBlock), 0, st, hits.off,
                hits.d_count, hits.n_tracks, n_rows, (const int32_t*)cnt, order);
+    TPC_LAUNCH(k_refit_pack,
+               dim3(grid_for_block(ceil_div(hits.n_tracks, kWave) * pack_parts(n_rows), 1, 65536)),
+               dim3(kBlock), 0, st,
+               (HitRows{hits.idx, hits.row, hits.y, hits.z, hits.off}), hits.d_count,
+               hits.n_tracks, n_rows, (const int32_t*)order, ck_packed(ck, hits.n_tracks, n_rows));
 }
 
 // the adjoint and its theta reduction, partials[16 * refit_grid(n_tracks)]
@@ -1061,9 +1303,10 @@ static int launch_refit_adjoint(tpc_track_hits hits, int32_t n_rows, const float
 {
     const CalibModel cm = make_calib(m);
     const unsigned nb = refit_grid(hits.n_tracks);
-    TPC_LAUNCH(k_refit_adj, dim3(nb), dim3(kWave), 0, st, hits.off, hits.idx, hits.row, hits.y,
-               hits.z, hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x, prm, cm,
-               d_theta, checkpoints, status, grad_chi2, seed_p, seed_x, grad_y, grad_z, partials,
+    TPC_LAUNCH(k_refit_adj, dim3(nb), dim3(kWave), 0, st, hits.off,
+               ck_packed(checkpoints, hits.n_tracks, n_rows), hits.side, hits.d_count,
+               hits.n_tracks, n_rows, d_row_x, prm, cm, d_theta, checkpoints, status, grad_chi2,
+               seed_p, seed_x, grad_y, grad_z, partials,
                ck_order(checkpoints, hits.n_tracks, n_rows));
     TPC_LAUNCH(k_reduce_theta, dim3(16), dim3(kBlock), 0, st, (const double*)partials, (int)nb,
                grad_theta);
@@ -1145,11 +1388,23 @@ int tpc_refit(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows, const float
     const tpc::CalibModel cm = tpc::make_calib(*h_model);
     hipStream_t st = (hipStream_t)stream;
     if (checkpoints) tpc::launch_order(hits, n_rows, checkpoints, st);
-    TPC_LAUNCH(tpc::k_refit_fwd, dim3(tpc::refit_grid(hits.n_tracks)), dim3(tpc::kWave),
-                       0, st, hits.off, hits.idx, hits.row, hits.y, hits.z,
-                       hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x, *h_params, cm,
-                       d_theta, par, cov, chi2, status, checkpoints,
-                       checkpoints ? tpc::ck_order(checkpoints, hits.n_tracks, n_rows) : nullptr);
+    const tpc::HitRows in{hits.idx, hits.row, hits.y, hits.z, hits.off};
+    const dim3 g(tpc::refit_grid(hits.n_tracks));
+    if (checkpoints)
+        TPC_LAUNCH(tpc::k_refit_fwd<tpc::kPacked>, g, dim3(tpc::kWave), 0, st, in,
+                   tpc::ck_packed(checkpoints, hits.n_tracks, n_rows), hits.side, hits.d_count,
+                   hits.n_tracks, n_rows, d_row_x, *h_params, cm, d_theta, par, cov, chi2, status,
+                   checkpoints, tpc::ck_order(checkpoints, hits.n_tracks, n_rows));
+    else if (hits.idx)
+        TPC_LAUNCH(tpc::k_refit_fwd<tpc::kCsrIndex>, g, dim3(tpc::kWave), 0, st, in,
+                   tpc::PackedHits{}, hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x,
+                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints,
+                   (const int32_t*)nullptr);
+    else
+        TPC_LAUNCH(tpc::k_refit_fwd<tpc::kCsr>, g, dim3(tpc::kWave), 0, st, in,
+                   tpc::PackedHits{}, hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x,
+                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints,
+                   (const int32_t*)nullptr);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
 }
 
