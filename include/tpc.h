@@ -523,8 +523,9 @@ typedef struct tpc_track_hits {
  * must be well formed (off increasing, off[n_tracks] = n_hits).
  * checkpoints (nullable, ck_bytes long, at least tpc_refit_checkpoint_size
  * of the n_tracks member): the state and covariance after every update but
- * the last, for tpc_refit_adjoint, in a layout private to the library (tiles
- * of 64 tracks, 20 floats per hit slot; with a checkpoint buffer the tracks
+ * the last, or every second of them, for tpc_refit_adjoint, in a layout private to the library (tiles
+ * of 64 tracks, 20 floats per hit slot, from 65536 tracks per two; with a
+ * checkpoint buffer the tracks
  * are taken in order of decreasing hit count, equal counts in track order,
  * and that order and a copy of the hits by tile are kept in the buffer too:
  * the adjoint reads the hits there).  A shorter buffer is an

@@ -2,12 +2,13 @@
 //
 // Forward (one thread per track): calibrate every raw cluster with the 16
 // parameters theta, start from the first and third hits, filter outwards and
-// sum the chi2 of the updates; the state after every update but the last is
-// written as a checkpoint (5 parameters + 15 covariance entries).
+// sum the chi2 of the updates; the state after every update but the last (in
+// large sets after every second hit) is written as a checkpoint (5 parameters
+// + 15 covariance entries).
 //
 // Adjoint (one thread per track): with L = sum_k g_k chi2_k, a reverse sweep
 // from the last hit reloads each checkpoint, recomputes the transport and
-// update, and applies their exact derivatives: of the update (gain, chi2,
+// update (and the state between two checkpoints), and applies their exact derivatives: of the update (gain, chi2,
 // covariance) and of the transport including the dependence of the Jacobian
 // on the state and on the step length, which the calibration moves.  The
 // symmetric covariance carries a symmetric adjoint G with
@@ -17,8 +18,8 @@
 // What bounds them: few tracks, the serial chain of one track's hits, at 4.3
 // cycles per VALU instruction (forward 1.3 us a hit, then 0.85; adjoint 2.0,
 // then 1.55, on 400 tracks, with the short division and root sequences and
-// without waits for hits); many, the checkpoints (80 bytes a hit written and
-// read back).
+// without waits for hits); many, the checkpoints (80 or 40 bytes a hit
+// written and read back) and then the adjoint's instructions.
 #include <mutex>
 #include <type_traits>
 
@@ -446,15 +447,21 @@ __device__ __forceinline__ float prop_adj(const Prop& P, const float* p0, const 
     return dxb;
 }
 
-// Checkpoints are kept in tiles of 64 tracks (one wave): slot i of the
-// track in lane l of tile g holds 20 floats (p, C) as five float4 at
-// ck4[((g * n_rows + i) * 5 + q) * 64 + l].  The lanes of a wave that stand
+// Checkpoints are kept in tiles of 64 tracks (one wave): every `stride`-th
+// state of the track in lane l of tile g, slot j the state after hit
+// j * stride, holds 20 floats (p, C) as five float4 at
+// ck4[((g * slots + j) * 5 + q) * 64 + l].  The lanes of a wave that stand
 // at the same slot store and load five contiguous 1 KB blocks, and one
 // wave's checkpoints are one contiguous block.
-__device__ __forceinline__ float4* ck_tile(float* ck, int64_t t, int n_rows)
+__device__ __forceinline__ float4* ck_tile(float* ck, int64_t t, int slots)
 {
-    return reinterpret_cast<float4*>(ck) + (t / kWave) * (int64_t)n_rows * 5 * kWave +
+    return reinterpret_cast<float4*>(ck) + (t / kWave) * (int64_t)slots * 5 * kWave +
            (t & (kWave - 1));
+}
+
+__host__ __device__ inline int ck_slots(int n_rows, int stride)
+{
+    return (n_rows + stride - 1) / stride;
 }
 
 __device__ __forceinline__ void store_ck(float4* o, int i, const float* p, const float* C)
@@ -813,7 +820,7 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
     HitRows in, PackedHits packed, const int8_t* __restrict__ side, const int64_t* __restrict__ d_count,
     int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
     const float* __restrict__ d_theta, float* __restrict__ par, float* __restrict__ cov,
-    float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck,
+    float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck, int stride,
     const int32_t* __restrict__ order)
 {
     __shared__ float th[16];
@@ -850,7 +857,8 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
         // track (a lane past its own track stores its unchanged state, which
         // nothing reads), so that each store writes whole lines; the tile of
         // the last, partial wave is allocated in full
-        float4* ckt = kFrom == kPacked ? ck_tile(ck, tb + lane, n_rows) : nullptr;
+        float4* ckt =
+            kFrom == kPacked ? ck_tile(ck, tb + lane, ck_slots(n_rows, stride)) : nullptr;
         const int M_ck = M < n_rows ? M : n_rows;
         auto start = [&](const CalHit& h0, const CalHit& h2) {
             // state from the first and third hits
@@ -899,7 +907,7 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
                 r1 = r2;
                 if (alive && i + 2 < n) r2 = raw_at(hp, i + 2);
                 if (alive && i < n) step(cal(r, kNo));
-                if (i + 1 < M_ck) store_ck(ckt, i, p, C);
+                if (i + 1 < M_ck && (stride == 1 || !(i & 1))) store_ck(ckt, i / stride, p, C);
             }
             const int parts = pack_parts(n_rows);
             for (int k = 0; k < parts; ++k)
@@ -953,6 +961,7 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
 // one track, so that most of a line is written by one instruction.
 constexpr int kGrads = 16;
 
+template <int kStride>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
 void k_refit_adj(
     const int32_t* __restrict__ off, PackedHits packed, const int8_t* __restrict__ side,
@@ -995,7 +1004,7 @@ void k_refit_adj(
         const int M = wave_max(ne);
         if (M == 0) continue;
         const PackedCol hp = packed_col(packed, tb + lane, n_rows);
-        const float4* ckt = ck_tile(const_cast<float*>(ck), tb + lane, n_rows);
+        const float4* ckt = ck_tile(const_cast<float*>(ck), tb + lane, ck_slots(n_rows, kStride));
         const float sd = fit && side ? (float)side[t] : 1.0f;
         const float cb = fit ? gchi2[t] : 0.0f;
         // adjoint of the final state: the seed of the caller's terms in the
@@ -1011,27 +1020,43 @@ void k_refit_adj(
             return calibrate<end()>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
         };
         CalHit cur{};
-        RawHit r1{};       // hit of the coming slot, loaded a step ahead
-        // checkpoint of the coming step (slot i - 1), loaded a step ahead
+        // step i needs hit i - 1, with every second checkpoint hit i - 2 too;
+        // the raw hit of the next step's last need is loaded a step ahead
+        CalHit prev{};
+        RawHit r1{};
+        // the checkpoint at or below slot i - 1, loaded a step ahead
         float4 ck4[5];
         if (fit) {
             cur = cal(raw_at(hp, n - 1), kYes);
-            r1 = raw_at(hp, n - 2);
-            load_ck(ckt, n - 2, ck4);
+            if (kStride == 2) prev = cal(raw_at(hp, n - 2), kNo);
+            r1 = raw_at(hp, n - 1 - kStride);
+            load_ck(ckt, (n - 2) / kStride, ck4);
         }
         // dL/dx of the last hit's calibrated plane from the caller's terms
         float Xcarry = fit && seed_x ? seed_x[t] : 0.0f;
         float X2 = 0.0f, Y2 = 0.0f, Z2 = 0.0f;
-        // step i needs hit i - 1; the gradients leave kGrads slots at a time
+        // the gradients leave kGrads slots at a time
         for (int top = M - 1; top >= 1;) {
             const int lo = top / kGrads * kGrads > 1 ? top / kGrads * kGrads : 1;
             for (int i = top; i >= lo; --i) {
                 if (i >= ne) continue;
-                const CalHit prev = cal(r1, kNo);
-                if (i >= 2) r1 = raw_at(hp, i - 2);
+                const RawHit r2 = r1;
+                if (i > kStride) r1 = raw_at(hp, i - 1 - kStride);
+                CalHit next{};
+                if (kStride == 1) prev = cal(r2, kNo);
+                else if (i >= 2) next = cal(r2, kNo);
                 float p[5], C[15];
                 unpack_ck(ck4, p, C);
-                if (i >= 2) load_ck(ckt, i - 2, ck4);
+                if (kStride == 2 && !(i & 1)) {
+                    // the state after hit i - 1 from that after hit i - 2
+                    const float x0 = i == 2 ? cal(r2, kYes).x : next.x;
+                    Prop P;
+                    Upd U;
+                    prop_fwd(p, C, prev.x - x0, prm.curv, prm.s_max, P);
+                    upd_fwd(p, C, prev.y, prev.z, prm.sigma_y2, prm.sigma_z2, U);
+                } else if (i > kStride) {
+                    load_ck(ckt, (i - 1) / kStride - 1, ck4);
+                }
                 const float p0[5] = {p[0], p[1], p[2], p[3], p[4]};
                 Prop P;
                 prop_fwd(p, C, cur.x - prev.x, prm.curv, prm.s_max, P);
@@ -1053,6 +1078,7 @@ void k_refit_adj(
                 }
                 Xcarry = -dxb;
                 cur = prev;
+                if (kStride == 2) prev = next;
             }
             // hits lo .. top, but hit 2: kGrads lanes write one track's run
             const int i = lo + (lane & (kGrads - 1));
@@ -1228,6 +1254,16 @@ static unsigned refit_grid(int64_t n_tracks)
     return grid_for_block(n_tracks, kWave, kRefitMaxBlocks);
 }
 
+// Every state is a checkpoint, or every second one: half of the 80 bytes a
+// hit that bound large sets, for one more forward step per two hits in the
+// adjoint.  1M tracks (us, forward + adjoint): 2150 + 2490 with every state,
+// 1170 + 2160 with every second; 100,000: 256 + 352, 180 + 357; 400, where
+// the adjoint's chain of instructions is what counts: 135 + 246, 122 + 290.
+// The line lies where the tracks' waves fill the SIMDs.  (A device count
+// below n_tracks does not move it: 17,000 tracks in buffers for 440,000 lose
+// 40 us in the adjoint and win 10 in the forward pass.)
+constexpr int64_t kSparseTracks = int64_t(1) << 16;
+
 // The checkpoint buffer: the tiles, then the tile order (int32 per track),
 // the per-(key, block) counts of the ordering, its scan partials and the
 // packed hits.
@@ -1235,7 +1271,13 @@ struct CkLayout {
     size_t order_off, cnt_off, part_off, yz_off, row_off, bad_off, total;
     int64_t nblk;
     int nkeys;
+    int stride;
 };
+
+static int ck_stride(int64_t n_tracks)
+{
+    return n_tracks >= kSparseTracks ? 2 : 1;
+}
 
 static size_t ck_align(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -1246,7 +1288,9 @@ static CkLayout ck_layout(int64_t n_tracks, int n_rows)
     L.nblk = ceil_div(n_tracks > 0 ? n_tracks : 1, kOrdBlock);
     L.nkeys = n_rows + 2;
     const int64_t ncnt = L.nblk * L.nkeys;
-    L.order_off = ck_align(sizeof(float) * (size_t)tiles * kWave * (size_t)n_rows * 20);
+    L.stride = ck_stride(n_tracks);
+    L.order_off = ck_align(sizeof(float) * (size_t)tiles * kWave *
+                           (size_t)ck_slots(n_rows, L.stride) * 20);
     L.cnt_off = L.order_off + ck_align(sizeof(int32_t) * (size_t)(n_tracks > 0 ? n_tracks : 1));
     L.part_off = L.cnt_off + ck_align(sizeof(int32_t) * (size_t)ncnt);
     L.yz_off = L.part_off + ck_align(sizeof(int64_t) * (size_t)(ceil_div(ncnt, kScanTile) + 1));
@@ -1303,11 +1347,16 @@ static int launch_refit_adjoint(tpc_track_hits hits, int32_t n_rows, const float
 {
     const CalibModel cm = make_calib(m);
     const unsigned nb = refit_grid(hits.n_tracks);
-    TPC_LAUNCH(k_refit_adj, dim3(nb), dim3(kWave), 0, st, hits.off,
-               ck_packed(checkpoints, hits.n_tracks, n_rows), hits.side, hits.d_count,
-               hits.n_tracks, n_rows, d_row_x, prm, cm, d_theta, checkpoints, status, grad_chi2,
-               seed_p, seed_x, grad_y, grad_z, partials,
-               ck_order(checkpoints, hits.n_tracks, n_rows));
+    const PackedHits packed = ck_packed(checkpoints, hits.n_tracks, n_rows);
+    const int32_t* order = ck_order(checkpoints, hits.n_tracks, n_rows);
+    if (ck_stride(hits.n_tracks) == 2)
+        TPC_LAUNCH(k_refit_adj<2>, dim3(nb), dim3(kWave), 0, st, hits.off, packed, hits.side,
+                   hits.d_count, hits.n_tracks, n_rows, d_row_x, prm, cm, d_theta, checkpoints,
+                   status, grad_chi2, seed_p, seed_x, grad_y, grad_z, partials, order);
+    else
+        TPC_LAUNCH(k_refit_adj<1>, dim3(nb), dim3(kWave), 0, st, hits.off, packed, hits.side,
+                   hits.d_count, hits.n_tracks, n_rows, d_row_x, prm, cm, d_theta, checkpoints,
+                   status, grad_chi2, seed_p, seed_x, grad_y, grad_z, partials, order);
     TPC_LAUNCH(k_reduce_theta, dim3(16), dim3(kBlock), 0, st, (const double*)partials, (int)nb,
                grad_theta);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
@@ -1394,16 +1443,17 @@ int tpc_refit(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows, const float
         TPC_LAUNCH(tpc::k_refit_fwd<tpc::kPacked>, g, dim3(tpc::kWave), 0, st, in,
                    tpc::ck_packed(checkpoints, hits.n_tracks, n_rows), hits.side, hits.d_count,
                    hits.n_tracks, n_rows, d_row_x, *h_params, cm, d_theta, par, cov, chi2, status,
-                   checkpoints, tpc::ck_order(checkpoints, hits.n_tracks, n_rows));
+                   checkpoints, tpc::ck_stride(hits.n_tracks),
+                   tpc::ck_order(checkpoints, hits.n_tracks, n_rows));
     else if (hits.idx)
         TPC_LAUNCH(tpc::k_refit_fwd<tpc::kCsrIndex>, g, dim3(tpc::kWave), 0, st, in,
                    tpc::PackedHits{}, hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x,
-                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints,
+                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints, 1,
                    (const int32_t*)nullptr);
     else
         TPC_LAUNCH(tpc::k_refit_fwd<tpc::kCsr>, g, dim3(tpc::kWave), 0, st, in,
                    tpc::PackedHits{}, hits.side, hits.d_count, hits.n_tracks, n_rows, d_row_x,
-                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints,
+                   *h_params, cm, d_theta, par, cov, chi2, status, checkpoints, 1,
                    (const int32_t*)nullptr);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
 }

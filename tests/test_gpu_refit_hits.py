@@ -123,3 +123,34 @@ def test_refused_tracks(n_rows, gather):
         if st[k]:
             assert not bool(gy[sl].any()) and not bool(gz[sl].any())
     assert bool(torch.isfinite(gt).all())
+
+
+@pytest.mark.parametrize("n_tracks", [(1 << 16) - 1, 1 << 16, (1 << 16) + 37])
+def test_gradients_on_both_sides_of_the_checkpoint_rule(n_tracks):
+    """From 65536 tracks on every second state is a checkpoint: the same bits
+    for every track as in a small set, at every length class."""
+    rs = synth.make_config5(n_tracks=2000)
+    off, row, y, z = cut(rs, LENGTHS)
+    rx, th = torch.as_tensor(rs.row_x).cuda(), torch.as_tensor(rs.theta_eval).cuda()
+    n = len(LENGTHS)
+    small = hits(off, row, y, z, np.ones(n, np.int8), False)
+    # the same tracks over and over
+    reps = -(-n_tracks // n)
+    lens = np.tile(np.diff(off), reps)[:n_tracks]
+    big_off = np.zeros(n_tracks + 1, np.int32)
+    big_off[1:] = np.cumsum(lens)
+    m = int(big_off[-1])
+    big = hits(big_off, np.tile(row, reps)[:m], np.tile(y, reps)[:m], np.tile(z, reps)[:m],
+               np.ones(n_tracks, np.int8), False)
+    res = []
+    for h in (small, big):
+        out = api.refit(ctx(), h, rx, PRM, th)
+        gy, gz, _ = api.refit_adjoint(ctx(), h, rx, PRM, th, out,
+                                      torch.ones(h.n_tracks, device="cuda"))
+        res.append((out["par"], out["chi2"], gy, gz))
+    k = off[-1]
+    for a, b, w in zip(res[0], res[1], (n, n, k, k)):
+        tail = b.shape[0] % w
+        full = b[:b.shape[0] - tail].reshape(-1, w, *b.shape[1:])
+        assert torch.equal(bits(full), bits(a).expand(full.shape))
+        assert torch.equal(bits(b[b.shape[0] - tail:]), bits(a)[:tail])
