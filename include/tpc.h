@@ -523,14 +523,14 @@ typedef struct tpc_track_hits {
  * must be well formed (off increasing, off[n_tracks] = n_hits).
  * checkpoints (nullable, ck_bytes long, at least tpc_refit_checkpoint_size
  * of the n_tracks member): the state and covariance after every update but
- * the last, or every second of them, for tpc_refit_adjoint, in a layout private to the library (tiles
- * of 64 tracks, 20 floats per hit slot, from 65536 tracks per two; with a
- * checkpoint buffer the tracks
- * are taken in order of decreasing hit count, equal counts in track order,
- * and that order and a copy of the hits by tile are kept in the buffer too:
- * the adjoint reads the hits there).  A shorter buffer is an
- * argument error, as are n_hits or n_tracks of 2^31 or more.  Outputs do not
- * depend on the order; the adjoint's theta reduction follows it. */
+ * the last, or every second of them, for tpc_refit_adjoint, in a layout
+ * private to the library (tiles of 64 tracks, 20 floats per hit slot, from
+ * 65536 tracks per two; with a checkpoint buffer the tracks are taken in
+ * order of decreasing hit count, equal counts in track order, and that order
+ * and a copy of the hits by tile are kept in the buffer too: the adjoint
+ * reads the hits there).  A shorter buffer is an argument error, as are
+ * n_hits or n_tracks of 2^31 or more.  Outputs do not depend on the order;
+ * the adjoint's theta reduction follows it. */
 int tpc_refit(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows, const float* d_row_x,
               const tpc_params* h_params, const tpc_calib_model* h_model,
               const float* d_theta, float* par, float* cov, float* chi2, int32_t* status,

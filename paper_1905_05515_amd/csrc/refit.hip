@@ -638,9 +638,15 @@ __device__ __forceinline__ RawHit raw_at(const PackedCol& c, int i)
 // tile have similar lengths: a tile steps to its longest track, storing and
 // loading whole checkpoint lines, and tiles of uniformly drawn lengths would
 // otherwise move about 1.5 times the checkpoint bytes their tracks need.
-// A counting sort by key (n_rows + 1) - min(n, n_rows + 1): per block of
-// 256 tracks the key counts (one wave's equal keys found by nine ballots),
-// an exclusive scan over (key, block), then every track's position.
+// A counting sort by key (n_rows + 1) - min(n, n_rows + 1) in at most
+// kOrdRanges runs of tracks, cut from the count on the device: per run the
+// key counts (one wave's equal keys found by nine ballots), an exclusive scan
+// over (key, run), then every track's position.  What bounds it is the scan
+// and the launches: with one run per 256 tracks of the capacity the counts of
+// 17,000 tracks in buffers for 440,000 were 265,000 entries to clear and
+// scan, and those of a million 600,000 (59 and 88 us for the three kernels of
+// the ordering); with 512 runs they are at most 79,000 (RUNS_US).
+constexpr int kOrdRanges = 512;
 constexpr int kOrdBlock = 256;
 
 __device__ __forceinline__ int order_key(const int32_t* __restrict__ off, int64_t t, int n_rows)
@@ -662,21 +668,28 @@ __device__ __forceinline__ uint64_t same_key(int key)
     return m;
 }
 
-// wc[w][key]: count of the key among wave w's tracks of the block
-__device__ __forceinline__ void order_counts(const int32_t* __restrict__ off, int64_t nt,
-                                             int n_rows, int nkeys, int (*wc)[256 + 2], int& key,
-                                             int& rank)
+// tracks per run: whole blocks, so that a run's chunks are full
+__device__ __forceinline__ int64_t order_run(int64_t nt)
 {
-    for (int i = threadIdx.x; i < (kOrdBlock / kWave) * nkeys; i += kOrdBlock)
-        wc[i / nkeys][i % nkeys] = 0;
-    __syncthreads();
-    const int64_t t = blockIdx.x * (int64_t)kOrdBlock + threadIdx.x;
+    const int64_t chunks = (nt + kOrdBlock - 1) / kOrdBlock;
+    return (chunks + gridDim.x - 1) / gridDim.x * kOrdBlock;
+}
+
+// wc[w][key]: count of the key among wave w's tracks of the chunk at t0 (all
+// threads of the block; wc is zero on entry); true where the thread's track
+// is below end, key and rank (among the wave's equal keys) are then its own
+__device__ __forceinline__ bool order_counts(const int32_t* __restrict__ off, int64_t t0,
+                                             int64_t end, int n_rows, int (*wc)[256 + 2],
+                                             int& key, int& rank)
+{
+    const int64_t t = t0 + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
-    key = t < nt ? order_key(off, t, n_rows) : 511;   // 511: no track, no key
+    key = t < end ? order_key(off, t, n_rows) : 511;   // 511: no track, no key
     const uint64_t m = same_key(key);
     rank = __popcll(m & ((1ull << lane) - 1ull));
     if (key != 511 && rank == 0) wc[threadIdx.x / kWave][key] = __popcll(m);
     __syncthreads();
+    return key != 511;
 }
 
 __global__ __launch_bounds__(kOrdBlock) void k_order_count(const int32_t* __restrict__ off,
@@ -684,17 +697,31 @@ __global__ __launch_bounds__(kOrdBlock) void k_order_count(const int32_t* __rest
                                                            int64_t n_tracks, int n_rows,
                                                            int32_t* __restrict__ cnt)
 {
-    __shared__ int wc[kOrdBlock / kWave][256 + 2];
+    __shared__ int wc[kOrdBlock / kWave][256 + 2], sum[256 + 2];
     const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
     const int nkeys = n_rows + 2;
-    int key, rank;
-    order_counts(off, nt, n_rows, nkeys, wc, key, rank);
     for (int k = threadIdx.x; k < nkeys; k += kOrdBlock) {
-        int c = 0;
+        sum[k] = 0;
 #pragma unroll
-        for (int w = 0; w < kOrdBlock / kWave; ++w) c += wc[w][k];
-        cnt[(int64_t)k * gridDim.x + blockIdx.x] = c;
+        for (int w = 0; w < kOrdBlock / kWave; ++w) wc[w][k] = 0;
     }
+    __syncthreads();
+    const int64_t run = order_run(nt), t0 = blockIdx.x * run;
+    const int64_t end = t0 + run < nt ? t0 + run : nt;
+    for (int64_t t = t0; t < end; t += kOrdBlock) {
+        int key, rank;
+        order_counts(off, t, end, n_rows, wc, key, rank);
+        for (int k = threadIdx.x; k < nkeys; k += kOrdBlock) {
+#pragma unroll
+            for (int w = 0; w < kOrdBlock / kWave; ++w) {
+                sum[k] += wc[w][k];
+                wc[w][k] = 0;
+            }
+        }
+        __syncthreads();
+    }
+    for (int k = threadIdx.x; k < nkeys; k += kOrdBlock)
+        cnt[(int64_t)k * gridDim.x + blockIdx.x] = sum[k];
 }
 
 // after the scan of cnt: position of every track t < nt, order[pos] = t
@@ -704,14 +731,35 @@ __global__ __launch_bounds__(kOrdBlock) void k_order_place(const int32_t* __rest
                                                            const int32_t* __restrict__ base,
                                                            int32_t* __restrict__ order)
 {
-    __shared__ int wc[kOrdBlock / kWave][256 + 2];
+    __shared__ int wc[kOrdBlock / kWave][256 + 2], next[256 + 2];
     const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
-    int key, rank;
-    order_counts(off, nt, n_rows, n_rows + 2, wc, key, rank);
-    if (key == 511) return;
-    int pos = base[(int64_t)key * gridDim.x + blockIdx.x] + rank;
-    for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) pos += wc[w][key];
-    order[pos] = (int32_t)(blockIdx.x * (int64_t)kOrdBlock + threadIdx.x);
+    const int nkeys = n_rows + 2;
+    const int64_t run = order_run(nt), t0 = blockIdx.x * run;
+    const int64_t end = t0 + run < nt ? t0 + run : nt;
+    if (t0 >= end) return;
+    for (int k = threadIdx.x; k < nkeys; k += kOrdBlock) {
+        next[k] = base[(int64_t)k * gridDim.x + blockIdx.x];
+#pragma unroll
+        for (int w = 0; w < kOrdBlock / kWave; ++w) wc[w][k] = 0;
+    }
+    __syncthreads();
+    for (int64_t t = t0; t < end; t += kOrdBlock) {
+        int key, rank;
+        if (order_counts(off, t, end, n_rows, wc, key, rank)) {
+            int pos = next[key] + rank;
+            for (int w = 0; w < (int)(threadIdx.x / kWave); ++w) pos += wc[w][key];
+            order[pos] = (int32_t)(t + threadIdx.x);
+        }
+        __syncthreads();
+        for (int k = threadIdx.x; k < nkeys; k += kOrdBlock) {
+#pragma unroll
+            for (int w = 0; w < kOrdBlock / kWave; ++w) {
+                next[k] += wc[w][k];
+                wc[w][k] = 0;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // track of tile position q (q itself past the count, or without an order)
@@ -1131,15 +1179,32 @@ void k_refit_adj(
     }
 }
 
-// sum of the per-block partials in a fixed order: block k sums parameter k;
-// thread j adds partials j, j + 256, ... of it, then a fixed tree
+// sum of the partials of the blocks that had tracks, in a fixed order: block
+// k sums parameter k; thread j adds partials j, j + 256, ... of it, then a
+// fixed tree.  Bound by the latency of the strided loads, so eight are in
+// flight, and the blocks past the count on the device (their partials are
+// zero) are left out: 34 us -> REDUCE_US for 16,384 blocks, of which 266 had
+// tracks.
 __global__ __launch_bounds__(kBlock) void k_reduce_theta(const double* __restrict__ partials,
-                                                         int nb, float* __restrict__ out)
+                                                         int nb,
+                                                         const int64_t* __restrict__ d_count,
+                                                         int64_t n_tracks,
+                                                         float* __restrict__ out)
 {
     __shared__ double red[kBlock];
     const int k = blockIdx.x;
+    const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
+    const int64_t tiles = (nt + kWave - 1) / kWave;
+    const int nu = tiles < nb ? (int)tiles : nb;
     double v = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kBlock) v += partials[b * 16 + k];
+    for (int b = threadIdx.x; b < nu; b += 8 * kBlock) {
+        double p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            p[i] = b + i * kBlock < nu ? partials[(b + i * kBlock) * 16 + k] : 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v += p[i];
+    }
     red[threadIdx.x] = v;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
@@ -1265,7 +1330,7 @@ static unsigned refit_grid(int64_t n_tracks)
 constexpr int64_t kSparseTracks = int64_t(1) << 16;
 
 // The checkpoint buffer: the tiles, then the tile order (int32 per track),
-// the per-(key, block) counts of the ordering, its scan partials and the
+// the per-(key, run) counts of the ordering, its scan partials and the
 // packed hits.
 struct CkLayout {
     size_t order_off, cnt_off, part_off, yz_off, row_off, bad_off, total;
@@ -1286,6 +1351,7 @@ static CkLayout ck_layout(int64_t n_tracks, int n_rows)
     CkLayout L;
     const int64_t tiles = (n_tracks + kWave - 1) / kWave;
     L.nblk = ceil_div(n_tracks > 0 ? n_tracks : 1, kOrdBlock);
+    if (L.nblk > kOrdRanges) L.nblk = kOrdRanges;
     L.nkeys = n_rows + 2;
     const int64_t ncnt = L.nblk * L.nkeys;
     L.stride = ck_stride(n_tracks);
@@ -1358,7 +1424,7 @@ static int launch_refit_adjoint(tpc_track_hits hits, int32_t n_rows, const float
                    hits.d_count, hits.n_tracks, n_rows, d_row_x, prm, cm, d_theta, checkpoints,
                    status, grad_chi2, seed_p, seed_x, grad_y, grad_z, partials, order);
     TPC_LAUNCH(k_reduce_theta, dim3(16), dim3(kBlock), 0, st, (const double*)partials, (int)nb,
-               grad_theta);
+               hits.d_count, hits.n_tracks, grad_theta);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
 }
 

@@ -5,6 +5,8 @@ the packed parts of 64 slots), runs at every alignment, both z sides, and
 tracks that are refused (short, long, a row outside the table anywhere).
 The readers agree bit for bit, states and gradients; what they compute is
 compared with the float64 oracle in test_gpu_refit.py."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -154,3 +156,43 @@ def test_gradients_on_both_sides_of_the_checkpoint_rule(n_tracks):
         full = b[:b.shape[0] - tail].reshape(-1, w, *b.shape[1:])
         assert torch.equal(bits(full), bits(a).expand(full.shape))
         assert torch.equal(bits(b[b.shape[0] - tail:]), bits(a)[:tail])
+
+
+@pytest.mark.parametrize("n_tracks, count", [(131072, None), (131073, None), (300000, 262145),
+                                             (300000, 257), (300000, 0)])
+def test_order_of_many_runs(n_tracks, count):
+    """The ordering cuts the tracks into at most 512 runs of whole blocks: one
+    and two blocks a run, a device count far below the capacity; lengths drawn
+    at random, every track as in the reader without an order."""
+    rs = synth.make_config5(n_tracks=2000)
+    off, row, y, z = cut(rs, (40,))
+    rng = np.random.Generator(np.random.PCG64(11))
+    lens = rng.integers(1, 12, n_tracks)
+    big_off = np.zeros(n_tracks + 1, np.int32)
+    big_off[1:] = np.cumsum(lens)
+    pos = np.arange(int(big_off[-1])) - np.repeat(big_off[:-1], lens)
+    h = hits(big_off, row[pos], y[pos], z[pos], np.ones(n_tracks, np.int8), False)
+    if count is not None:
+        d_count = torch.tensor([count], dtype=torch.int64, device="cuda")
+        h.d_count = C.c_void_p(d_count.data_ptr())
+    n = n_tracks if count is None else count
+    rx, th = torch.as_tensor(rs.row_x).cuda(), torch.as_tensor(rs.theta_eval).cuda()
+    a = api.refit(ctx(), h, rx, PRM, th)
+    b = api.refit(ctx(), h, rx, PRM, th, checkpoints=False)
+    for k in ("par", "cov", "chi2", "status"):
+        assert torch.equal(bits(a[k][:n]), bits(b[k][:n])), k
+    gy, gz, gt = api.refit_adjoint(ctx(), h, rx, PRM, th, a,
+                                   torch.ones(n_tracks, device="cuda"))
+    m = int(big_off[n])
+    # every track of one length has the same hits: the same gradients
+    for g in (gy, gz):
+        g = g[:m].cpu().numpy()
+        for c in range(3, 12):
+            t = np.flatnonzero(lens[:n] == c)
+            at = big_off[t][:, None] + np.arange(c)[None, :]
+            v = g[at].view(np.int32)
+            assert (v == v[:1]).all()
+            if t.size:
+                assert g[at[0]].any()
+    assert bool(torch.isfinite(gt).all())
+    assert bool(gt.any()) == (n > 0)
