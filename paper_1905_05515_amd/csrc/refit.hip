@@ -641,11 +641,11 @@ __device__ __forceinline__ RawHit raw_at(const PackedCol& c, int i)
 // A counting sort by key (n_rows + 1) - min(n, n_rows + 1) in at most
 // kOrdRanges runs of tracks, cut from the count on the device: per run the
 // key counts (one wave's equal keys found by nine ballots), an exclusive scan
-// over (key, run), then every track's position.  What bounds it is the scan
-// and the launches: with one run per 256 tracks of the capacity the counts of
-// 17,000 tracks in buffers for 440,000 were 265,000 entries to clear and
-// scan, and those of a million 600,000 (59 and 88 us for the three kernels of
-// the ordering); with 512 runs they are at most 79,000 (RUNS_US).
+// over (key, run), then every track's position.  What bounds it is the
+// launches and the counts: with one run per 256 tracks of the capacity, the
+// ordering and its scan took 64 us for the 17,000 tracks that 512 sectors
+// leave in buffers many times that size, and now 19; a million tracks take
+// 32 either way.
 constexpr int kOrdRanges = 512;
 constexpr int kOrdBlock = 256;
 
@@ -1183,8 +1183,9 @@ void k_refit_adj(
 // k sums parameter k; thread j adds partials j, j + 256, ... of it, then a
 // fixed tree.  Bound by the latency of the strided loads, so eight are in
 // flight, and the blocks past the count on the device (their partials are
-// zero) are left out: 34 us -> REDUCE_US for 16,384 blocks, of which 266 had
-// tracks.
+// zero) are left out: 33 us -> 4.4 for the 17,000 tracks of 512 sectors in
+// their far larger buffers (16,384 blocks),
+// 34 -> 23 for a million.
 __global__ __launch_bounds__(kBlock) void k_reduce_theta(const double* __restrict__ partials,
                                                          int nb,
                                                          const int64_t* __restrict__ d_count,
