@@ -136,7 +136,6 @@ int tpc_track_batch(tpc_context* ctx, const tpc_problem* h_prob, tpc_clusters in
         } else if (mode == TPC_MODE_PER_SECTOR) {
             // every stage sector by sector, then one dense compaction of the
             // track list over all tracklets
-            tpc::launch_fill<uint64_t>(ws.tlen, 0ull, count_cap + 1, st);
             for (int s = 0; s < ns && !r; ++s) {
                 r = tpc::run_build_grid(h_prob, s, s + 1, in, grid, ws, st);
                 if (!r)

@@ -48,4 +48,12 @@ __device__ inline T block_sum(T v, T* lds)
     return tot;
 }
 
+// Sum of partials[0, b) by one block (every thread gets it).
+__device__ inline int64_t sum_before(const int64_t* __restrict__ partials, int64_t b, int64_t* lds)
+{
+    int64_t s = 0;
+    for (int64_t k = threadIdx.x; k < b; k += kBlock) s += partials[k];
+    return block_sum(s, lds);
+}
+
 }  // namespace tpc

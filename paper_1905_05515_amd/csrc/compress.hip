@@ -757,7 +757,7 @@ int tpc_compress_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_clust
     TPC_LAUNCH(tpc::k_cz_rowcount, dim3(tpc::grid_for(nrs * tpc::kWave)), dim3(tpc::kBlock), 0, st,
                h_prob->d_sectors, n_sec, n_rows, (const int32_t*)grid.bin_start,
                (const int32_t*)grid.id, w);
-    tpc::launch_scan<int32_t>(w.rowcnt, w.rowcnt, nrs, false, nullptr, nullptr, w.partials, st);
+    tpc::launch_scan<int32_t>(w.rowcnt, w.rowcnt, nrs, false, nullptr, w.partials, st);
     TPC_LAUNCH(tpc::k_cz_rowemit, dim3(tpc::grid_for(nrs * tpc::kWave)), dim3(tpc::kBlock), 0, st,
                h_prob->d_sectors, n_sec, n_rows, (const int32_t*)grid.bin_start,
                (const int32_t*)grid.id, clusters.y, clusters.z, charge,
@@ -772,7 +772,7 @@ int tpc_compress_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_clust
     for (int k = 0; k < tpc::kStreams; ++k) {
         TPC_LAUNCH(tpc::k_cz_eflag, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st, w,
                    k);
-        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, w.eoff + k, nullptr,
+        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, w.eoff + k,
                                   w.partials, st);
     }
     TPC_LAUNCH(tpc::k_cz_layout, dim3(1), dim3(tpc::kBlock), 0, st, w, (int)cp.cbits, (int)cp.qbits,
@@ -782,7 +782,7 @@ int tpc_compress_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_clust
     for (int k = 0; k < tpc::kStreams; ++k) {
         TPC_LAUNCH(tpc::k_cz_eflag, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st, w,
                    k);
-        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, nullptr, nullptr,
+        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, nullptr,
                                   w.partials, st);
         TPC_LAUNCH(tpc::k_cz_copy_esc, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st,
                    w, k, out);

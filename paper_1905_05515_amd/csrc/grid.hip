@@ -56,13 +56,34 @@ __device__ __forceinline__ int tile_setup(const tpc_sector* __restrict__ sec, in
 
 constexpr int kTileSecMax = 8;
 
+// what the build counts in, zero; the status block (whole on the first call
+// of an event) with the grid positions the build will have written
+__global__ __launch_bounds__(kBlock) void k_grid_clear(tpc_status* status, int first,
+                                                       int64_t n_grid, int32_t* __restrict__ rcnt,
+                                                       int32_t* __restrict__ rfill, int64_t nbk,
+                                                       int32_t* __restrict__ bigq)
+{
+    if (blockIdx.x == 0) {
+        int64_t* w = reinterpret_cast<int64_t*>(status);
+        if (first)
+            for (int k = threadIdx.x; k < (int)(sizeof(tpc_status) / 8); k += blockDim.x) w[k] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            status->n_grid = n_grid;
+            bigq[0] = 0;   // the list of step 5
+        }
+    }
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nbk;
+         i += (int64_t)gridDim.x * blockDim.x)
+        rcnt[i] = rfill[i] = 0;
+}
+
 // ts: sectors of a tile with LDS counters (Rb * ts <= kTileCounters)
 __global__ __launch_bounds__(kBlock) void k_grid_rows(
     const tpc_sector* __restrict__ sec, int n_sec, int n_rows, int S, int ts,
     const uint8_t* __restrict__ row, const float* __restrict__ z, int64_t c0, int64_t c1,
-    int32_t* __restrict__ rcnt, tpc_status* status, int32_t* __restrict__ bigq)
+    int32_t* __restrict__ rcnt, tpc_status* status)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) bigq[0] = 0;   // the list of step 5
     __shared__ int hist[kTileCounters];
     __shared__ int64_t ends[kTileSecMax];
     __shared__ int sf_sh;
@@ -200,11 +221,6 @@ __global__ __launch_bounds__(kBlock) void k_grid_place(
     }
 }
 
-__global__ void k_set_grid_status(tpc_status* status, int64_t n_grid)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) status->n_grid = n_grid;
-}
-
 // Build the grid of sectors [sec_lo, sec_hi).  The first call of an event
 // (sec_lo == 0) clears the status block.
 int run_build_grid(const tpc_problem* p, int sec_lo, int sec_hi, tpc_clusters in,
@@ -220,14 +236,13 @@ int run_build_grid(const tpc_problem* p, int sec_lo, int sec_hi, tpc_clusters in
     if (ts < 1) ts = 1;
     if (Rb > kTileCounters) return TPC_ERR_UNSUPPORTED;
     const int64_t nbk = (int64_t)(sec_hi - sec_lo) * Rb;
-    if (sec_lo == 0) launch_fill<int64_t>((int64_t*)ws.status, 0, sizeof(tpc_status) / 8, st);
-    launch_fill<int32_t>(ws.rcnt + (int64_t)sec_lo * Rb, 0, nbk, st);
-    launch_fill<int32_t>(ws.rfill + (int64_t)sec_lo * Rb, 0, nbk, st);
+    TPC_LAUNCH(k_grid_clear, dim3(grid_for(nbk)), dim3(kBlock), 0, st, ws.status, sec_lo == 0, c1,
+               ws.rcnt + (int64_t)sec_lo * Rb, ws.rfill + (int64_t)sec_lo * Rb, nbk, ws.bigq);
     const unsigned gt = grid_for_block(ceil_div(c1 - c0, kRowTile), 1, 4096);
     TPC_LAUNCH(k_grid_rows, dim3(gt), dim3(kBlock), 0, st, p->d_sectors, p->n_sectors,
-               p->n_rows, S, ts, in.row, in.z, c0, c1, ws.rcnt, ws.status, ws.bigq);
+               p->n_rows, S, ts, in.row, in.z, c0, c1, ws.rcnt, ws.status);
     launch_scan<int32_t>(ws.rcnt + (int64_t)sec_lo * Rb, ws.rstart + (int64_t)sec_lo * Rb, nbk,
-                         true, nullptr, nullptr, ws.partials, st, c0);
+                         true, nullptr, ws.partials, st, c0);
     TPC_LAUNCH(k_grid_rows_scatter, dim3(gt), dim3(kBlock), 0, st, p->d_sectors, p->n_sectors,
                p->n_rows, S, ts, in.row, in.y, in.z, c0, c1, (const int32_t*)ws.rstart,
                ws.rfill, ws.tmp, ws.gy, ws.gz);
@@ -254,7 +269,6 @@ int run_build_grid(const tpc_problem* p, int sec_lo, int sec_hi, tpc_clusters in
                (const int32_t*)out.bin_start, (const int32_t*)ws.tmp, (const float*)ws.gy,
                (const float*)ws.gz, (const int32_t*)ws.gslot, (const int32_t*)ws.gbin,
                (const int32_t*)ws.gtag, out.y, out.z, out.id, ws.gsr);
-    TPC_LAUNCH(k_set_grid_status, dim3(1), dim3(1), 0, st, ws.status, c1);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
 }
 

@@ -1393,7 +1393,7 @@ static void launch_order(const tpc_track_hits& hits, int n_rows, float* ck, hipS
     int64_t* part = reinterpret_cast<int64_t*>(b + L.part_off);
     TPC_LAUNCH(k_order_count, dim3((unsigned)L.nblk), dim3(kOrdBlock), 0, st, hits.off,
                hits.d_count, hits.n_tracks, n_rows, cnt);
-    launch_scan<int32_t>(cnt, cnt, L.nblk * L.nkeys, false, nullptr, nullptr, part, st);
+    launch_scan<int32_t>(cnt, cnt, L.nblk * L.nkeys, false, nullptr, part, st);
     TPC_LAUNCH(k_order_place, dim3((unsigned)L.nblk), dim3(kOrdBlock), 0, st, hits.off,
                hits.d_count, hits.n_tracks, n_rows, (const int32_t*)cnt, order);
     TPC_LAUNCH(k_refit_pack,

@@ -294,8 +294,8 @@ __device__ __forceinline__ void neighbours_one(
 
 // Mutual links of the hit at p; a chain start (up link, no down link, and
 // its up neighbour has an up link) is flagged in the id-indexed array
-// start_by_id.
-__device__ __forceinline__ void clean_one(
+// start_by_id; returns its id, -1 for any other hit.
+__device__ __forceinline__ int clean_one(
     int64_t p, const int32_t* __restrict__ up0, const int32_t* __restrict__ down0,
     const int32_t* __restrict__ idg, int32_t* __restrict__ up, int32_t* __restrict__ down,
     int32_t* __restrict__ start_by_id)
@@ -307,8 +307,13 @@ __device__ __forceinline__ void clean_one(
     down[p] = dc;
     if (uc >= 0 && dc < 0) {
         const int uu = up0[uc];
-        if (uu >= 0 && down0[uu] == uc) start_by_id[idg[p]] = (int32_t)p;
+        if (uu >= 0 && down0[uu] == uc) {
+            const int id = idg[p];
+            start_by_id[id] = (int32_t)p;
+            return id;
+        }
     }
+    return -1;
 }
 
 }  // namespace tpc

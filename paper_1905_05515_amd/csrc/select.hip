@@ -3,6 +3,7 @@
 // at least min_tracklet_hits hits (64-bit atomic max, order independent); a
 // tracklet keeping at least min_track_hits clusters becomes a track.
 // Tracks are compacted in tracklet order by a scan of (accepted, kept).
+#include "block_dev.hpp"
 #include "select_dev.hpp"
 
 namespace tpc {
@@ -211,19 +212,82 @@ __global__ __launch_bounds__(kBlock) void k_sel_count_bits(
     }
 }
 
-// per tracklet: 1 << 32 | kept if it becomes a track, else 0
+// Per tracklet found: 1 << 32 | kept if it becomes a track, else 0, and the
+// sum of every tile.  Tiles past the tracklets found leave at once (over the
+// whole capacity, with a pass to clear it, this and the scan took 60 us more
+// on 512 sectors).
 __global__ __launch_bounds__(kBlock) void k_sel_len(
-    int n_chunks, tpc_params prm, const int64_t* __restrict__ t_lo,
-    const int64_t* __restrict__ t_hi, int64_t count_cap, const uint8_t* __restrict__ ccnt,
-    uint64_t* __restrict__ tlen)
+    int n_chunks, tpc_params prm, const tpc_status* __restrict__ status, int64_t count_cap,
+    const uint8_t* __restrict__ ccnt, uint64_t* __restrict__ tlen, int64_t* __restrict__ partials)
 {
-    const int64_t lo = *t_lo < count_cap ? *t_lo : count_cap;
-    const int64_t m = *t_hi < count_cap ? *t_hi : count_cap;
-    for (int64_t t = lo + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < m;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        int kept = 0;
-        for (int q = 0; q < n_chunks; ++q) kept += ccnt[q * count_cap + t];
-        tlen[t] = kept >= prm.min_track_hits ? ((1ull << 32) | (uint64_t)kept) : 0ull;
+    __shared__ uint64_t lds[kBlock / kWave];
+    const int64_t m = status->n_starts < count_cap ? status->n_starts : count_cap;
+    const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+    if (b0 >= m) {
+        if (threadIdx.x == 0) partials[blockIdx.x] = 0;
+        return;
+    }
+    int kept[kScanItems] = {};
+#pragma unroll 4
+    for (int q = 0; q < n_chunks; ++q)
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            const int64_t t = b0 + k * kBlock + threadIdx.x;
+            kept[k] += ccnt[q * count_cap + (t < m ? t : m - 1)];
+        }
+    uint64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        const int64_t t = b0 + k * kBlock + threadIdx.x;
+        if (t >= m) continue;
+        const uint64_t v =
+            kept[k] >= prm.min_track_hits ? ((1ull << 32) | (uint64_t)kept[k]) : 0ull;
+        tlen[t] = v;
+        s += v;
+    }
+    const uint64_t tot = block_sum(s, lds);
+    if (threadIdx.x == 0) partials[blockIdx.x] = (int64_t)tot;
+}
+
+// toff: exclusive scan of tlen over the tracklets found (kSelf: the tiles'
+// sums before are added here, else they are scanned); the tile of the last
+// tracklet writes the counts of tracks and hits.
+template <bool kSelf>
+__global__ __launch_bounds__(kBlock) void k_sel_offsets(
+    const uint64_t* __restrict__ tlen, const int64_t* __restrict__ partials, int64_t count_cap,
+    uint64_t* __restrict__ toff, tpc_status* __restrict__ status, int32_t* __restrict__ trk_off,
+    int64_t trk_cap, int64_t hit_cap)
+{
+    __shared__ uint64_t lds[kBlock / kWave];
+    __shared__ int64_t lds64[kBlock / kWave];
+    const int64_t m = status->n_starts < count_cap ? status->n_starts : count_cap;
+    const int64_t b0 = (int64_t)blockIdx.x * kScanTile;
+    if (b0 >= m && blockIdx.x > 0) return;
+    const int64_t base = b0 + (int64_t)threadIdx.x * kScanItems;
+    uint64_t v[kScanItems];
+    uint64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        v[k] = base + k < m ? tlen[base + k] : 0ull;
+        s += v[k];
+    }
+    const uint64_t before = (uint64_t)(kSelf ? sum_before(partials, blockIdx.x, lds64)
+                                             : partials[blockIdx.x]);
+    uint64_t tot;
+    uint64_t ex = block_excl_scan(s, lds, &tot) + before;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        if (base + k < m) toff[base + k] = ex;
+        ex += v[k];
+    }
+    if (threadIdx.x == 0 && b0 + kScanTile >= m) {
+        const uint64_t all = before + tot;
+        const int64_t nt = (int64_t)(all >> 32), nh = (int64_t)(all & 0xFFFFFFFFull);
+        status->n_tracks = nt;
+        status->n_track_hits = nh;
+        if (nt <= trk_cap) trk_off[nt] = (int32_t)nh;
+        if (nt > trk_cap) status->overflow |= 2;
+        if (nh > hit_cap) status->overflow |= 4;
     }
 }
 
@@ -253,19 +317,6 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(
         const uint64_t key = key_of(t, prm, idg, t_start, t_nhits);
         sel_write_chunk(t, q * kSelRows, n_rows, key, o, idg, t_hits, cap, hitkey, out, hit_cap);
     }
-}
-
-__global__ void k_sel_finish(const uint64_t* __restrict__ toff_total, tpc_status* status,
-                             int32_t* __restrict__ trk_off, int64_t trk_cap, int64_t hit_cap)
-{
-    if (blockIdx.x || threadIdx.x) return;
-    const uint64_t tot = *toff_total;
-    const int64_t nt = (int64_t)(tot >> 32), nh = (int64_t)(tot & 0xFFFFFFFFull);
-    status->n_tracks = nt;
-    status->n_track_hits = nh;
-    if (nt <= trk_cap) trk_off[nt] = (int32_t)nh;
-    if (nt > trk_cap) status->overflow |= 2;
-    if (nh > hit_cap) status->overflow |= 4;
 }
 
 // Track hits from their grid positions (written by k_sel_write in track
@@ -373,18 +424,29 @@ int run_select_keys(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
                    n_words, (const unsigned long long*)ws.tkey,
                    (const unsigned long long*)ws.kbits, ws.ccnt);
     }
-    TPC_LAUNCH(k_sel_len, dim3(gx), dim3(kBlock), 0, st, nq, p->params, lo, hi, count_cap,
-               (const uint8_t*)ws.ccnt, ws.tlen);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
 }
 
 // Dense track list in tracklet order from the kept-hit counts of all
-// tracklets [0, count_cap) (tlen zero where no track).
+// tracklets found, at most count_cap.
 int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
                        tpc_tracklets trl, tpc_tracks trk, const Workspace& ws, hipStream_t st)
 {
     const unsigned gx = sel_grid_x(count_cap);
-    launch_scan<uint64_t>(ws.tlen, ws.toff, count_cap, true, nullptr, nullptr, ws.partials, st);
+    const int64_t nt = ceil_div(count_cap > 0 ? count_cap : 1, kScanTile);
+    TPC_LAUNCH(k_sel_len, dim3((unsigned)nt), dim3(kBlock), 0, st, sel_chunks(p->n_rows),
+               p->params, (const tpc_status*)ws.status, count_cap, (const uint8_t*)ws.ccnt,
+               ws.tlen, ws.partials);
+    if (nt <= kScanSelf) {
+        TPC_LAUNCH(k_sel_offsets<true>, dim3((unsigned)nt), dim3(kBlock), 0, st,
+                   (const uint64_t*)ws.tlen, (const int64_t*)ws.partials, count_cap, ws.toff,
+                   ws.status, trk.off, trk.capacity, trk.hit_capacity);
+    } else {
+        launch_scan_partials(ws.partials, nt, nullptr, nullptr, st);
+        TPC_LAUNCH(k_sel_offsets<false>, dim3((unsigned)nt), dim3(kBlock), 0, st,
+                   (const uint64_t*)ws.tlen, (const int64_t*)ws.partials, count_cap, ws.toff,
+                   ws.status, trk.off, trk.capacity, trk.hit_capacity);
+    }
     TPC_LAUNCH(k_sel_write, dim3(gx, sel_chunks(p->n_rows)), dim3(kBlock), 0, st, p->n_rows,
                p->params, (const int32_t*)grid.id, (const int32_t*)trl.start,
                (const int32_t*)trl.hits, (const int32_t*)trl.nhits, (const tpc_status*)ws.status,
@@ -395,8 +457,6 @@ int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
                          nullptr, nullptr},
                trk.tracklet, trk.side,
                trk.capacity, trk.hit_capacity);
-    TPC_LAUNCH(k_sel_finish, dim3(1), dim3(1), 0, st, (const uint64_t*)(ws.toff + count_cap),
-               ws.status, trk.off, trk.capacity, trk.hit_capacity);
     const int64_t hb = trk.hit_capacity < p->n_clusters ? trk.hit_capacity : p->n_clusters;
     TPC_LAUNCH(k_trk_copy, dim3(grid_for(ceil_div(hb, 4))), dim3(kBlock), 0, st,
                (const tpc_status*)ws.status, hb, (const int32_t*)ws.tpos,
@@ -408,7 +468,6 @@ int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
 int run_select_tracks(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
                       tpc_tracklets trl, tpc_tracks trk, const Workspace& ws, hipStream_t st)
 {
-    launch_fill<uint64_t>(ws.tlen, 0ull, count_cap + 1, st);
     int r = run_select_keys(p, 0, p->n_sectors, grid, count_cap, trl, ws, st);
     if (!r) r = run_select_compact(p, grid, count_cap, trl, trk, ws, st);
     return r;

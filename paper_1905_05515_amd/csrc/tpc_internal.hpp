@@ -27,8 +27,8 @@ struct Workspace {
     int32_t* gsr;          // [n] sector << 8 | row per grid position
     int64_t* partials;     // scan tile partials
     uint64_t* hitkey;      // [n] selection keys per grid position
-    uint64_t* tlen;        // [start_cap + 1] per tracklet: accepted << 32 | kept
-    uint64_t* toff;        // [start_cap + 1] exclusive scan of tlen
+    uint64_t* tlen;        // [start_cap + 1] per tracklet found: accepted << 32 | kept
+    uint64_t* toff;        // [start_cap + 1] exclusive scan of tlen, tracklets found
     uint8_t* ccnt;         // [row chunks * start_cap] kept hits per tracklet and row chunk
     uint64_t* tkey;        // [start_cap] selection, big sectors: key per tracklet
     uint64_t* kbits;       // [n_rows * sel_words(start_cap)] selection, big sectors: kept bits
@@ -173,13 +173,19 @@ struct TimerScope {
 template <typename T>
 void launch_fill(T* p, T v, int64_t n, hipStream_t st);
 
-// Exclusive scan of in[0..n) into out[0..n), starting from carry0 +
-// *carry_in (device, nullable: 0); out[n] = carry + total when write_total;
-// *total_dst (device, nullable) = carry + total.  in may equal out.
+// Exclusive scan of in[0..n) into out[0..n), starting from carry0;
+// out[n] = carry0 + total when write_total; *total_dst (device, nullable) =
+// carry0 + total.  in may equal out.
 template <typename T>
 void launch_scan(const T* in, T* out, int64_t n, bool write_total, int64_t* total_dst,
-                 const int64_t* carry_in, int64_t* partials, hipStream_t st,
-                 int64_t carry0 = 0);
+                 int64_t* partials, hipStream_t st, int64_t carry0 = 0);
+
+// Scans of at most this many tiles are two launches, the tile sums and the
+// tiles (one launch when there is a single tile): every tile adds the sums
+// before it itself, at most 8 KB from the L2, where a launch between the two
+// would cost 4.5 us.  Beyond, one block scans the sums: re-reading them grows
+// with the square of the tiles (34,000 of them: 4.6 GB).
+constexpr int64_t kScanSelf = 1024;
 
 // Exclusive scan, in place, of nt int64 tile partials by one block.
 void launch_scan_partials(int64_t* partials, int64_t nt, const int64_t* carry_in,

@@ -26,8 +26,6 @@ void launch_fill(T* p, T v, int64_t n, hipStream_t st)
     TPC_LAUNCH(k_fill<T>, dim3(grid_for(n, 8192)), dim3(kBlock), 0, st, p, v, n);
 }
 template void launch_fill<int32_t>(int32_t*, int32_t, int64_t, hipStream_t);
-template void launch_fill<uint64_t>(uint64_t*, uint64_t, int64_t, hipStream_t);
-template void launch_fill<int64_t>(int64_t*, int64_t, int64_t, hipStream_t);
 
 // phase 1: sum of every tile
 template <typename T>
@@ -74,13 +72,16 @@ __global__ __launch_bounds__(kBlock) void k_scan_partials(int64_t* __restrict__ 
     if (threadIdx.x == 0 && total_dst) *total_dst = carry;
 }
 
-// phase 3: scan inside every tile plus its offset
-template <typename T>
+// phase 3: scan inside every tile plus its offset.  kSelf: the partials are
+// still the tiles' sums, and every tile adds those before it to carry0.
+template <typename T, bool kSelf>
 __global__ __launch_bounds__(kBlock) void k_scan_tiles(const T* in, T* out, int64_t n,
                                                        const int64_t* __restrict__ partials,
+                                                       int64_t carry0, int64_t* total_dst,
                                                        int write_total)
 {
     __shared__ T lds[kBlock / kWave];
+    __shared__ int64_t lds64[kBlock / kWave];
     int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     T v[kScanItems];
     T s = 0;
@@ -89,8 +90,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const T* in, T* out, int6
         v[k] = (base + k < n) ? in[base + k] : T(0);
         s += v[k];
     }
+    const int64_t before =
+        kSelf ? carry0 + sum_before(partials, blockIdx.x, lds64) : partials[blockIdx.x];
     T tot;
-    T ex = block_excl_scan(s, lds, &tot) + (T)partials[blockIdx.x];
+    T ex = block_excl_scan(s, lds, &tot) + (T)before;
+    if (kSelf && total_dst && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        *total_dst = before + (int64_t)tot;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (base + k < n) out[base + k] = ex;
@@ -101,15 +106,20 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const T* in, T* out, int6
 
 template <typename T>
 void launch_scan(const T* in, T* out, int64_t n, bool write_total, int64_t* total_dst,
-                 const int64_t* carry_in, int64_t* partials, hipStream_t st, int64_t carry0)
+                 int64_t* partials, hipStream_t st, int64_t carry0)
 {
     int64_t nt = ceil_div(n > 0 ? n : 1, kScanTile);
-    TPC_LAUNCH(k_scan_tile_sums<T>, dim3((unsigned)nt), dim3(kBlock), 0, st, in, n,
-                       partials);
-    TPC_LAUNCH(k_scan_partials, dim3(1), dim3(kBlock), 0, st, partials, nt, carry_in, carry0,
-                       total_dst);
-    TPC_LAUNCH(k_scan_tiles<T>, dim3((unsigned)nt), dim3(kBlock), 0, st, in, out, n,
-                       (const int64_t*)partials, write_total ? 1 : 0);
+    if (nt > 1)
+        TPC_LAUNCH(k_scan_tile_sums<T>, dim3((unsigned)nt), dim3(kBlock), 0, st, in, n, partials);
+    if (nt <= kScanSelf) {
+        TPC_LAUNCH((k_scan_tiles<T, true>), dim3((unsigned)nt), dim3(kBlock), 0, st, in, out, n,
+                   (const int64_t*)partials, carry0, total_dst, write_total ? 1 : 0);
+        return;
+    }
+    TPC_LAUNCH(k_scan_partials, dim3(1), dim3(kBlock), 0, st, partials, nt, (const int64_t*)nullptr,
+               carry0, total_dst);
+    TPC_LAUNCH((k_scan_tiles<T, false>), dim3((unsigned)nt), dim3(kBlock), 0, st, in, out, n,
+               (const int64_t*)partials, carry0, total_dst, write_total ? 1 : 0);
 }
 void launch_scan_partials(int64_t* partials, int64_t nt, const int64_t* carry_in,
                           int64_t* total_dst, hipStream_t st)
@@ -118,10 +128,8 @@ void launch_scan_partials(int64_t* partials, int64_t nt, const int64_t* carry_in
                (int64_t)0, total_dst);
 }
 
-template void launch_scan<int32_t>(const int32_t*, int32_t*, int64_t, bool, int64_t*,
-                                   const int64_t*, int64_t*, hipStream_t, int64_t);
-template void launch_scan<uint64_t>(const uint64_t*, uint64_t*, int64_t, bool, int64_t*,
-                                    const int64_t*, int64_t*, hipStream_t, int64_t);
+template void launch_scan<int32_t>(const int32_t*, int32_t*, int64_t, bool, int64_t*, int64_t*,
+                                   hipStream_t, int64_t);
 
 // ---- workspace ----------------------------------------------------------------
 
