@@ -142,7 +142,7 @@ __device__ __forceinline__ void tracklet_task(const PArgs& a, const float* xs, f
         const int64_t tb = lo + (int64_t)c * kWave;
         if (tb >= hi) break;
         const int64_t t = tb + lane;
-        build_tracklets((uint32_t)t, t < hi, a.sec, a.n_rows, xs, a.prm, a.grid.bin_start,
+        build_tracklets((uint32_t)t, nullptr, t < hi, a.sec, a.n_rows, xs, a.prm, a.grid.bin_start,
                         a.grid.y, a.grid.z, a.grid.id, a.ws.gsr, a.links.up, a.starts,
                         a.trl.hits, a.trl.capacity, keep, a.trl.start, a.trl.nhits,
                         a.trl.row_inner, a.trl.par, a.trl.cov, a.trl.chi2, n_prop, n_upd,

@@ -277,10 +277,11 @@ __device__ __forceinline__ void keep_state(float4* keep, const KState& st)
     keep[4 * kWave] = make_float4(st.C[11], st.C[12], st.C[13], st.C[14]);
 }
 
-// Build the tracklets of one wave, tracklet t in each lane with `act` (every
-// lane of the wave calls).  xs holds the row positions; the hit list (grid
-// position per row, -1 where none) is column t of t_hits[row][cap]; keep:
-// the lane's slot of kKeepVec float4 in LDS.
+// Build the tracklets of one wave, one in each lane with `act` (every lane
+// of the wave calls): tracklet ord[q], or q where there is no order.  xs
+// holds the row positions; the hit list (grid position per row, -1 where
+// none) is column q of t_hits[row][cap]; keep: the lane's slot of kKeepVec
+// float4 in LDS.
 //
 // Up pass: from the start hit, one row at a time, the next hit is the next
 // link of the chain while there is one (links always join adjacent rows),
@@ -298,7 +299,8 @@ __device__ __forceinline__ void keep_state(float4* keep, const KState& st)
 // and write one row of the hit lists as one line, where lanes each at their
 // own row read their own lines and wrote single words.
 __device__ __forceinline__ void build_tracklets(
-    uint32_t t, bool act, const tpc_sector* __restrict__ sec, int n_rows, const float* xs,
+    uint32_t q, const int32_t* __restrict__ ord, bool act, const tpc_sector* __restrict__ sec,
+    int n_rows, const float* xs,
     const tpc_params& prm, const int32_t* __restrict__ bin_start, const float* __restrict__ yg,
     const float* __restrict__ zg, const int32_t* __restrict__ idg,
     const int32_t* __restrict__ gsr, const int32_t* __restrict__ up,
@@ -308,9 +310,9 @@ __device__ __forceinline__ void build_tracklets(
     int& n_prop, int& n_upd, int& n_cand)   // of the wave; of the wave; of the lane
 {
     const float sy2 = prm.sigma_y2, sz2 = prm.sigma_z2;
-    // a tracklet has three clusters of its own: t < 2^31 / 3, a 32-bit byte
+    // a tracklet has three clusters of its own: q < 2^31 / 3, a 32-bit byte
     // offset from the row's (uniform) base
-    const uint32_t tb = t * 4u;
+    const uint32_t tb = q * 4u;
     auto hit_at = [&](int r) -> int32_t& {
         return *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(t_hits + r * cap) + tb);
     };
@@ -320,6 +322,7 @@ __device__ __forceinline__ void build_tracklets(
     int cc = -1, cn = -1;                 // chain hit of the coming row, of the one after
     float cy = 0.0f, cz = 0.0f;
     if (act) {
+        const uint32_t t = ord ? (uint32_t)ord[q] : q;
         const int h0 = starts[t];
         const int v0 = gsr[h0];
         s = sec[v0 >> 8];
@@ -470,16 +473,17 @@ __device__ __forceinline__ void build_tracklets(
         n_upd += __popcll(__ballot(upd));
     }
     if (!act) return;
+    const uint32_t t = ord ? (uint32_t)ord[q] : q;
     t_nhits[t] = nh;
     t_rin[t] = rin;
     float v[20];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        const float4 k = keep[q * kWave];
-        v[4 * q] = k.x;
-        v[4 * q + 1] = k.y;
-        v[4 * q + 2] = k.z;
-        v[4 * q + 3] = k.w;
+    for (int i = 0; i < 5; ++i) {
+        const float4 k = keep[i * kWave];
+        v[4 * i] = k.x;
+        v[4 * i + 1] = k.y;
+        v[4 * i + 2] = k.z;
+        v[4 * i + 3] = k.w;
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) t_par[(int64_t)t * 5 + i] = v[i];
