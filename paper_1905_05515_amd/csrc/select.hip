@@ -8,14 +8,19 @@
 
 namespace tpc {
 
-// Sectors whose row chunks hold on average several times more positions
-// than the LDS table take the row form below instead (same keys and
-// counts).  A chunk just over the table still uses its
-// block (with device-wide keys).  Host and device decide alike from the
+// Sectors whose row chunks nearly fill the LDS table on average take the row
+// form below instead (same keys and counts).  The line lies below the
+// table's size because rows differ, and a chunk over the table uses its block
+// with device-wide keys: time frames of 4, 8, 16 and 40 collisions (chunks of
+// 4100, 8200, 16,000 and 41,000 positions on average) take 86, 1346, 3050 and
+// 8380 us by chunk and 122, 204, 407 and 1000 by row, one of 5 (5100, some
+// tables full) 143 by row and 330 with half of its sectors by chunk; 512
+// sector instances (21,000 clusters on average, up to 94,000) 142 by chunk,
+// 181 with their ten largest by row.  Host and device decide alike from the
 // sector's size.
 __host__ __device__ inline bool sel_big(const tpc_sector& s, int n_rows)
 {
-    return (s.end - s.begin) * (int64_t)kSelRows > (int64_t)(8 * kSelLds) * n_rows;
+    return (s.end - s.begin) * (int64_t)kSelRows > (int64_t)(kSelLds * 13 / 16) * n_rows;
 }
 
 // one block per (sector, row chunk) of sectors [sec_lo, ...)
@@ -56,7 +61,7 @@ constexpr int kSelRowUnroll = 4;          // tracklet entries loaded together
 constexpr unsigned long long kKeyNotBig = ~0ull;   // tracklet of a sector that is not big
 
 // tkey[t]: the tracklet's key (0: takes no part), kKeyNotBig outside big
-// sectors; kbits cleared over the words of tracklets [lo, m).
+// sectors; kbits of tracklets [lo, m) cleared.
 __global__ __launch_bounds__(kBlock) void k_sel_prep_big(
     const tpc_sector* __restrict__ sec, int n_rows, tpc_params prm,
     const int32_t* __restrict__ idg, const int32_t* __restrict__ gsr,
@@ -74,8 +79,12 @@ __global__ __launch_bounds__(kBlock) void k_sel_prep_big(
                                                             : kKeyNotBig;
     if (m <= lo) return;
     const int64_t w0 = lo >> 6, nw = ((m - 1) >> 6) - w0 + 1;
-    for (int64_t i = g; i < nw * n_rows; i += stride)
-        kbits[(i / nw) * n_words + w0 + i % nw] = 0ull;
+    // the first word keeps the bits of the tracklets before lo
+    const unsigned long long before = (1ull << (lo & 63)) - 1ull;
+    for (int64_t i = g; i < nw * n_rows; i += stride) {
+        unsigned long long* w = kbits + (i / nw) * n_words + w0 + i % nw;
+        *w = i % nw == 0 && before ? *w & before : 0ull;
+    }
 }
 
 // Keys in LDS: 32 bits when the sector has at most 2^24 clusters
@@ -105,9 +114,34 @@ struct Key64 {
     __device__ unsigned long long unpack(T k) const { return k; }
 };
 
+// k-th big sector of [sec_lo, sec_lo + n_sec) (all threads of the block)
+__device__ __forceinline__ int nth_big(const tpc_sector* __restrict__ sec, int sec_lo, int n_sec,
+                                       int n_rows, int k, int* cnt, int* found)
+{
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    int seen = 0;
+    for (int b = 0; b < n_sec; b += kSelRowBlock) {
+        const int i = b + (int)threadIdx.x;
+        const bool big = i < n_sec && sel_big(sec[sec_lo + i], n_rows);
+        const uint64_t m = __ballot(big);
+        if (lane == 0) cnt[wid] = __popcll(m);
+        __syncthreads();
+        int at = seen;
+        for (int w = 0; w < kSelRowBlock / kWave; ++w) {
+            if (w < wid) at += cnt[w];
+            seen += cnt[w];
+        }
+        if (big && at + __popcll(m & ((1ull << lane) - 1ull)) == k) *found = sec_lo + i;
+        __syncthreads();
+        if (seen > k) break;
+    }
+    return *found;
+}
+
+// n_big: big sectors of the range (all of them: no search for the block's)
 template <typename KF>
 __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
-    const tpc_sector* __restrict__ sec, int sec_lo, int n_rows,
+    const tpc_sector* __restrict__ sec, int sec_lo, int n_sec, int n_big, int n_rows,
     const int32_t* __restrict__ bin_start, const int32_t* __restrict__ t_hits,
     const int64_t* __restrict__ sec_start, int64_t count_cap, int64_t cap, int64_t n_words,
     const unsigned long long* __restrict__ tkey, unsigned long long* __restrict__ hitkey,
@@ -116,10 +150,12 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
     using T = typename KF::T;
     constexpr int kLds = kSelRowBytes / (int)sizeof(T);
     __shared__ T kl[kLds];
-    const int si = sec_lo + (int)(blockIdx.x / n_rows);
+    __shared__ int found, wave_big[kSelRowBlock / kWave];
+    const int k_big = (int)(blockIdx.x / n_rows);
+    const int si = n_big == n_sec ? sec_lo + k_big
+                                  : nth_big(sec, sec_lo, n_sec, n_rows, k_big, wave_big, &found);
     const int r = (int)(blockIdx.x % n_rows);
     const tpc_sector s = sec[si];
-    if (!sel_big(s, n_rows)) return;
     const KF kf{s.begin};
     const int per_row = s.nbz * s.nby;
     const int p0 = bin_start[s.bin_base + r * per_row];
@@ -191,24 +227,43 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
 }
 
 // Kept counts per row chunk of the tracklets of big sectors from the bits.
+// A block takes kBitWords words of every row, whole lines, into LDS; a wave
+// then counts one word's 64 tracklets, each lane its bit of the rows in turn
+// (one address a step: broadcast).  Bound by reading the bits; with every
+// lane loading its row's word by itself the 3.0M tracklets of a time frame
+// took 660 us, now 106.
+constexpr int kBitWords = 16;
+
 __global__ __launch_bounds__(kBlock) void k_sel_count_bits(
     int n_rows, const int64_t* __restrict__ t_lo, const int64_t* __restrict__ t_hi,
     int64_t count_cap, int64_t n_words, const unsigned long long* __restrict__ tkey,
     const unsigned long long* __restrict__ kbits, uint8_t* __restrict__ ccnt)
 {
+    __shared__ unsigned long long bits[256][kBitWords];
     const int64_t lo = *t_lo < count_cap ? *t_lo : count_cap;
     const int64_t m = *t_hi < count_cap ? *t_hi : count_cap;
-    for (int64_t t = lo + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < m;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        if (tkey[t] == kKeyNotBig) continue;     // k_sel_chunk counts it
-        const int64_t w = t >> 6;
-        const int b = (int)(t & 63);
-        for (int ra = 0, q = 0; ra < n_rows; ra += kSelRows, ++q) {
-            const int rb = ra + kSelRows < n_rows ? ra + kSelRows : n_rows;
-            int kept = 0;
-            for (int rr = ra; rr < rb; ++rr) kept += (int)((kbits[(int64_t)rr * n_words + w] >> b) & 1ull);
-            ccnt[q * count_cap + t] = (uint8_t)kept;
+    if (m <= lo) return;
+    const int64_t w_lo = lo >> 6, w_hi = ((m - 1) >> 6) + 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int64_t w0 = w_lo / kBitWords * kBitWords + blockIdx.x * (int64_t)kBitWords; w0 < w_hi;
+         w0 += (int64_t)gridDim.x * kBitWords) {
+        const int x = threadIdx.x % kBitWords;
+        for (int r = threadIdx.x / kBitWords; r < n_rows; r += kBlock / kBitWords)
+            bits[r][x] = w0 + x >= w_lo && w0 + x < w_hi ? kbits[(int64_t)r * n_words + w0 + x] : 0ull;
+        __syncthreads();
+        for (int k = threadIdx.x / kWave; k < kBitWords; k += kBlock / kWave) {
+            const int64_t t = ((w0 + k) << 6) + lane;
+            // outside the range, or counted by k_sel_chunk
+            if (t < lo || t >= m || tkey[t] == kKeyNotBig) continue;
+            for (int ra = 0, q = 0; ra < n_rows; ra += kSelRows, ++q) {
+                int kept = 0;
+#pragma unroll
+                for (int j = 0; j < kSelRows; ++j)
+                    if (ra + j < n_rows) kept += (int)((bits[ra + j][k] >> lane) & 1ull);
+                ccnt[q * count_cap + t] = (uint8_t)kept;
+            }
         }
+        __syncthreads();
     }
 }
 
@@ -291,6 +346,36 @@ __global__ __launch_bounds__(kBlock) void k_sel_offsets(
     }
 }
 
+// The kept hits of one row chunk of a big sector's tracklet: the bits tell
+// which, where the general form reads the key of every hit's position (3.9 GB
+// fetched and 1920 us on the time frame, now 1440).
+__device__ __forceinline__ void sel_write_bits(int64_t t, int ra, int n_rows, int64_t o,
+                                               const int32_t* __restrict__ t_hits, int64_t cap,
+                                               const unsigned long long* __restrict__ kbits,
+                                               int64_t n_words, const TrkHitOut& out,
+                                               int64_t hit_cap)
+{
+    unsigned long long b[kSelRows];
+#pragma unroll
+    for (int k = 0; k < kSelRows; ++k)
+        b[k] = ra + k < n_rows ? kbits[(int64_t)(ra + k) * n_words + (t >> 6)] : 0ull;
+    int c[kSelRows];
+#pragma unroll
+    for (int k = 0; k < kSelRows; ++k) {
+        c[k] = -1;
+        if ((b[k] >> (t & 63)) & 1ull) c[k] = t_hits[(int64_t)(ra + k) * cap + t];
+    }
+#pragma unroll
+    for (int k = 0; k < kSelRows; ++k)
+        if (c[k] >= 0) {
+            if (o < hit_cap) {
+                out.pos[o] = c[k];
+                if (out.row) out.row[o] = (uint8_t)(ra + k);
+            }
+            ++o;
+        }
+}
+
 __global__ __launch_bounds__(kBlock) void k_sel_write(
     int n_rows, tpc_params prm, const int32_t* __restrict__ idg,
     const int32_t* __restrict__ t_start, const int32_t* __restrict__ t_hits,
@@ -299,7 +384,9 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(
     const uint64_t* __restrict__ toff, const uint8_t* __restrict__ ccnt,
     const tpc_sector* __restrict__ sec, const int32_t* __restrict__ gsr,
     int32_t* __restrict__ trk_off, TrkHitOut out, int32_t* __restrict__ trk_tracklet,
-    int8_t* __restrict__ trk_side, int64_t trk_cap, int64_t hit_cap)
+    int8_t* __restrict__ trk_side, int64_t trk_cap, int64_t hit_cap,
+    const unsigned long long* __restrict__ tkey, const unsigned long long* __restrict__ kbits,
+    int64_t n_words)
 {
     int64_t m = status->n_starts;
     if (m > count_cap) m = count_cap;
@@ -314,6 +401,10 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(
                             trk_side, trk_cap);
         if (!ccnt[q * count_cap + t]) continue;     // the chunk keeps nothing
         for (int j = 0; j < q; ++j) o += ccnt[j * count_cap + t];
+        if (kbits && tkey[t] != kKeyNotBig) {
+            sel_write_bits(t, q * kSelRows, n_rows, o, t_hits, cap, kbits, n_words, out, hit_cap);
+            continue;
+        }
         const uint64_t key = key_of(t, prm, idg, t_start, t_nhits);
         sel_write_chunk(t, q * kSelRows, n_rows, key, o, idg, t_hits, cap, hitkey, out, hit_cap);
     }
@@ -375,6 +466,14 @@ __global__ __launch_bounds__(kBlock) void k_trk_copy(
     }
 }
 
+// Is any sector of the problem big?  (Then every call marks its tracklets.)
+static bool any_sel_big(const tpc_problem* p)
+{
+    for (int s = 0; s < p->n_sectors; ++s)
+        if (sel_big(p->h_sectors[s], p->n_rows)) return true;
+    return false;
+}
+
 static unsigned sel_grid_x(int64_t n) { return grid_for_block(n, kBlock, 1024); }
 
 // Ownership keys and kept-hit counts of the tracklets of sectors
@@ -393,9 +492,7 @@ int run_select_keys(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
                (const int32_t*)grid.id, (const int32_t*)trl.start, (const int32_t*)trl.hits,
                (const int32_t*)trl.nhits, (const int64_t*)ws.sec_start, count_cap,
                trl.capacity, (unsigned long long*)ws.hitkey, ws.ccnt);
-    bool any_big = false;
-    for (int s = sec_lo; s < sec_hi && !any_big; ++s) any_big = sel_big(p->h_sectors[s], p->n_rows);
-    if (any_big) {
+    if (any_sel_big(p)) {
         const int64_t n_words = sel_words(count_cap);
         TPC_LAUNCH(k_sel_prep_big, dim3(gx), dim3(kBlock), 0, st, p->d_sectors, p->n_rows,
                    p->params, (const int32_t*)grid.id, (const int32_t*)ws.gsr,
@@ -407,17 +504,19 @@ int run_select_keys(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
             if (sel_big(p->h_sectors[s], p->n_rows) &&
                 p->h_sectors[s].end - p->h_sectors[s].begin > (int64_t(1) << 24))
                 k32 = false;
-        const dim3 gr((unsigned)((sec_hi - sec_lo) * p->n_rows));
-        if (k32)
+        int n_big = 0;
+        for (int s = sec_lo; s < sec_hi; ++s) n_big += sel_big(p->h_sectors[s], p->n_rows);
+        const dim3 gr((unsigned)(n_big * p->n_rows));
+        if (n_big && k32)
             TPC_LAUNCH(k_sel_rows_big<Key32>, gr, dim3(kSelRowBlock), 0, st, p->d_sectors, sec_lo,
-                       p->n_rows, (const int32_t*)grid.bin_start, (const int32_t*)trl.hits,
-                       (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
+                       sec_hi - sec_lo, n_big, p->n_rows, (const int32_t*)grid.bin_start,
+                       (const int32_t*)trl.hits, (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
                        (const unsigned long long*)ws.tkey, (unsigned long long*)ws.hitkey,
                        (unsigned long long*)ws.kbits);
-        else
+        else if (n_big)
             TPC_LAUNCH(k_sel_rows_big<Key64>, gr, dim3(kSelRowBlock), 0, st, p->d_sectors, sec_lo,
-                       p->n_rows, (const int32_t*)grid.bin_start, (const int32_t*)trl.hits,
-                       (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
+                       sec_hi - sec_lo, n_big, p->n_rows, (const int32_t*)grid.bin_start,
+                       (const int32_t*)trl.hits, (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
                        (const unsigned long long*)ws.tkey, (unsigned long long*)ws.hitkey,
                        (unsigned long long*)ws.kbits);
         TPC_LAUNCH(k_sel_count_bits, dim3(gx), dim3(kBlock), 0, st, p->n_rows, lo, hi, count_cap,
@@ -455,8 +554,10 @@ int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
                p->d_sectors, (const int32_t*)ws.gsr, trk.off,
                TrkHitOut{ws.tpos, nullptr, trk.hit_y ? trk.hit_row : nullptr, nullptr, nullptr,
                          nullptr, nullptr},
-               trk.tracklet, trk.side,
-               trk.capacity, trk.hit_capacity);
+               trk.tracklet, trk.side, trk.capacity, trk.hit_capacity,
+               (const unsigned long long*)ws.tkey,
+               (const unsigned long long*)(any_sel_big(p) ? ws.kbits : nullptr),
+               sel_words(count_cap));
     const int64_t hb = trk.hit_capacity < p->n_clusters ? trk.hit_capacity : p->n_clusters;
     TPC_LAUNCH(k_trk_copy, dim3(grid_for(ceil_div(hb, 4))), dim3(kBlock), 0, st,
                (const tpc_status*)ws.status, hb, (const int32_t*)ws.tpos,

@@ -30,12 +30,13 @@ __device__ __forceinline__ int wave_starts(int64_t count, int64_t slots)
 // of a lone chain lane, ~520 where lanes search, and waits a third of its
 // time for the search's two dependent loads); many starts, VALU issue (on a
 // 64-collision time frame, 3.0M starts, the SIMDs issue VALU 98% of the
-// time; its sectors' starts are ordered, see below).  Walking the rows of a wave in step took 180,000 starts of
-// 512 sector instances from 1386 to 930 us and the time frame's 23.1 to 12.6 ms
-// (each lane at its own row fetched 5.2 GB past the L2s on the former); a form
-// with the hit lists in LDS, a fifth of the waves in flight, was no faster
-// on small events any more, nor was a queue form that refills idle lanes
-// (27.4 ms on the time frame).  // 128 VGPRs hold four waves a SIMD (137, and three waves: 13.9 ms).
+// time; its sectors' starts are ordered, see below).  Walking the rows of a
+// wave in step took 180,000 starts of 512 sector instances from 1386 to 930 us
+// and the time frame's 23.1 to 12.6 ms (each lane at its own row fetched
+// 5.2 GB past the L2s on the former); a form with the hit lists in LDS, a
+// fifth of the waves in flight, was no faster on small events any more, nor
+// was a queue form that refills idle lanes (27.4 ms on the time frame).
+// 128 VGPRs hold four waves a SIMD (137, and three waves: 13.9 ms).
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void k_tracklets(
     const tpc_sector* __restrict__ sec, int n_rows, const float* __restrict__ row_x,
@@ -44,8 +45,8 @@ void k_tracklets(
     const int32_t* __restrict__ gsr, const int32_t* __restrict__ up,
     const int32_t* __restrict__ starts, tpc_status* __restrict__ status,
     const int64_t* __restrict__ t_lo, const int64_t* __restrict__ t_hi, int64_t count_cap,
-    int64_t cap, int64_t slots, const int32_t* __restrict__ ord, int32_t* __restrict__ t_start, int32_t* __restrict__ t_hits,
-    int32_t* __restrict__ t_nhits, int32_t* __restrict__ t_rin, float* __restrict__ t_par,
+    int64_t cap, int64_t slots, const int32_t* __restrict__ ord, int32_t* __restrict__ t_start,
+    int32_t* __restrict__ t_hits, int32_t* __restrict__ t_nhits, int32_t* __restrict__ t_rin, float* __restrict__ t_par,
     float* __restrict__ t_cov, float* __restrict__ t_chi2)
 {
     __shared__ float4 keep[kKeepVec];
@@ -297,13 +298,17 @@ int run_construct_tracklets(const tpc_problem* p, int sec_lo, int sec_hi, tpc_gr
     int64_t g = ceil_div(n_launch, kWave);
     g = g < few ? few : g;
     g = g < 1 ? 1 : g > 65536 ? 65536 : g;
-    // the processing order of big sectors; the arrays of the selection's
-    // lengths hold it meanwhile
-    int64_t big = 0;
+    // the processing order, where big sectors hold half of the clusters (the
+    // sort and the way back visit every sector); the arrays of the
+    // selection's lengths hold it meanwhile
+    int64_t big = 0, in_big = 0;
     for (int i = sec_lo; i < sec_hi; ++i) {
         const tpc_sector& s = p->h_sectors[i];
-        if (sort_sector(s) && s.end - s.begin > big) big = s.end - s.begin;
+        if (!sort_sector(s)) continue;
+        in_big += s.end - s.begin;
+        if (s.end - s.begin > big) big = s.end - s.begin;
     }
+    if (in_big * 2 < p->h_sectors[sec_hi - 1].end - p->h_sectors[sec_lo].begin) big = 0;
     const int groups = (int)ceil_div(big / 3 + 1, kSortMax);
     int32_t* ord = big ? reinterpret_cast<int32_t*>(ws.tlen) : nullptr;
     uint16_t* inv = reinterpret_cast<uint16_t*>(ws.toff);

@@ -54,7 +54,8 @@ def make(kind):
     if kind == "long_row":
         return with_long_row(stacked(14))
     small = synth.make_config2(seed=6, n_primary=2000)
-    return joined([small.sector(3), stacked(15), small.sector(5)])
+    k = dict(mixed=[15], around_the_line=[9, 10, 11])[kind]
+    return joined([small.sector(3)] + [stacked(i) for i in k] + [small.sector(5)])
 
 
 @pytest.mark.parametrize("kind,cap", [("one_group", None), ("groups", None), ("long_row", None),
@@ -85,3 +86,16 @@ def test_same_as_the_order_of_the_starts(kind, cap):
         c = run_gpu(ev)[1]
         for k in INTS:
             assert np.array_equal(a[k], c[k]), k
+
+
+def test_selection_forms_side_by_side():
+    """Sectors of 86,000, 95,000 and 105,000 clusters between small ones: the
+    larger two select by row, the others by chunk; their tracklets share words
+    of the kept bits.  Every form gives the same tracks."""
+    ev = make("around_the_line")
+    print(np.diff(ev.sector_offsets), flush=True)
+    a = run_gpu(ev, mode="persistent")[1]
+    for mode in ("staged", "per_sector"):
+        b = run_gpu(ev, mode=mode)[1]
+        for k in INTS:
+            assert np.array_equal(a[k], b[k]), (mode, k)
