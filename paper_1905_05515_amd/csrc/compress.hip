@@ -22,8 +22,8 @@
 // header and symbols; one wave per (sector, row) counts, then (after a
 // scan) writes the other clusters' symbols; per-stream histograms in LDS;
 // one block per stream normalises its table; one thread per chunk encodes
-// backwards into the end of its chunk slot; scans order the escapes; one
-// block lays out the blob; copies place chunks, escapes and headers.
+// backwards into the end of its chunk slot; one block lays out the blob;
+// copies place chunks, escapes (in order, from counts per tile) and headers.
 #include "block_dev.hpp"
 #include "tracklet_dev.hpp"
 
@@ -43,7 +43,7 @@ struct CmpWs {
     uint8_t* on;            // [n_clusters] cluster on a track
     uint8_t* sym[kStreams];  // [cap_k] symbols
     int32_t* esc[kStreams];  // [cap_k] escaped value at an escape's position
-    int32_t* eflag;         // [max cap] escape flags of one stream, then positions
+    int32_t* ecnt;          // [kStreams][etiles] escapes of every tile, then those before it
     int32_t* rowcnt;        // [n_rowseg + 1] other clusters per (sector, row), then offsets
     uint8_t* hdr;           // [track cap * 16]
     uint32_t* hist;         // [kStreams * 256]
@@ -57,6 +57,7 @@ struct CmpWs {
     int64_t* lay;           // [kStreams * 3 + 4] blob offsets (chunk data, escapes, headers)
     int64_t* partials;      // scan partials
     int64_t cap[kStreams];
+    int64_t etiles;         // tiles of kScanTile symbols per stream, at most
     int64_t chunk_cap;      // chunks per stream, at most
     int64_t slot;           // bytes per chunk slot
     int64_t n_rowseg;
@@ -76,8 +77,7 @@ __device__ __forceinline__ uint32_t charge_code(float charge, int cbits)
     const uint32_t v = r < 0.0f ? 0u : r > 65535.0f ? 65535u : (uint32_t)r;
     const uint32_t top = 1u << cbits;
     if (v < top) return v;
-    int e = 0;
-    while ((v >> e) >= top) ++e;
+    const int e = 32 - __builtin_clz(v) - cbits;    // least with v >> e below top
     const uint32_t half = top >> 1;
     return top + (uint32_t)(e - 1) * half + ((v >> e) - half);
 }
@@ -116,12 +116,16 @@ __global__ __launch_bounds__(kBlock) void k_cz_mark(const int32_t* __restrict__ 
         w.on[hits[j]] = 1;
 }
 
-// one thread per track: header, hit count, row steps, residuals, charges.
+// One thread per track: header, hit count, row steps, residuals, charges.
 // A hit's row, y and z come from the track-ordered copies where the tracks
 // carry them (contiguous per track), else through the cluster index; the
-// next hit's values are loaded while the current one is filtered.
+// next hit's values are loaded while the current one is filtered, its index
+// a step earlier still, and the row positions are in LDS.  Bound by the chain
+// of the longest track, some 270 VALU instructions a hit, and by its waits:
+// a wait for the next hit's values is one for the stores before them too, so
+// symbols leave 8 at a time.  Central event, 16,800 tracks: 230 -> 169 us.
 __global__ __launch_bounds__(kBlock) void k_cz_tracks(
-    const float* __restrict__ row_x, tpc_params prm, const uint8_t* __restrict__ row,
+    const float* __restrict__ row_x, int n_rows, tpc_params prm, const uint8_t* __restrict__ row,
     const float* __restrict__ y, const float* __restrict__ z, const float* __restrict__ charge,
     const int32_t* __restrict__ off, const int32_t* __restrict__ hits,
     const uint8_t* __restrict__ h_row, const float* __restrict__ h_y,
@@ -129,6 +133,9 @@ __global__ __launch_bounds__(kBlock) void k_cz_tracks(
     const float* __restrict__ t_par, const int32_t* __restrict__ t_rin,
     const int64_t* __restrict__ d_n_tracks, int64_t cap, float inv_q, int cbits, CmpWs w)
 {
+    __shared__ float xs[256];
+    for (int i = threadIdx.x; i < n_rows; i += blockDim.x) xs[i] = row_x[i];
+    __syncthreads();
     const bool copies = h_row != nullptr;
     const int64_t nt = track_count(d_n_tracks, cap);
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nt;
@@ -154,15 +161,23 @@ __global__ __launch_bounds__(kBlock) void k_cz_tracks(
         st.p[3] = (float)t / 16384.0f;
         st.p[4] = (float)wq / 1024.0f;
         reset_cov(st, prm);
-        float x = row_x[(uint8_t)rin];
+        float x = xs[(uint8_t)rin];
         const int a = off[k], b = off[k + 1];
         put(w, S_LEN, k, (uint32_t)(b - a), b - a);
         bool alive = true;
+        // the last symbols of the four streams, 8 to a store
+        uint64_t s_row = 0, s_dy = 0, s_dz = 0, s_q = 0;
+        auto symbol = [&](uint64_t& acc, int str, int64_t i, uint32_t v, int32_t raw) {
+            acc = (acc >> 8) | ((uint64_t)(v < 255u ? v : 255u) << 56);
+            if (v >= 255u) w.esc[str][i] = raw;
+        };
         int prow = (uint8_t)rin;
         int r_n = 0;
-        float y_n = 0.0f, z_n = 0.0f, q_n = 0.0f, x_n = 0.0f;
+        float y_n = 0.0f, z_n = 0.0f, q_n = 0.0f;
+        int c_n = a < b ? hits[a] : 0;      // index of the hit to fetch next
         auto fetch = [&](int jj) {
-            const int c = hits[jj];
+            const int c = c_n;
+            if (jj + 1 < b) c_n = hits[jj + 1];
             if (copies) {
                 r_n = h_row[jj];
                 y_n = h_y[jj];
@@ -173,26 +188,39 @@ __global__ __launch_bounds__(kBlock) void k_cz_tracks(
                 z_n = z[c];
             }
             q_n = charge[c];
-            x_n = row_x[r_n];
         };
         if (a < b) fetch(a);
         for (int j = a; j < b; ++j) {
             const int r = r_n;
-            const float yc = y_n, zc = z_n, qc = q_n, xr = x_n;
+            const float yc = y_n, zc = z_n, qc = q_n, xr = xs[r];
             if (j + 1 < b) fetch(j + 1);
-            put(w, S_ROW, j, (uint32_t)(r - prow), r - prow);
+            symbol(s_row, S_ROW, j, (uint32_t)(r - prow), r - prow);
             prow = r;
             const int32_t cy = quant(yc, inv_q), cz = quant(zc, inv_q);
             if (alive && !propagate(st, xr - x, prm.curv, prm.s_max)) alive = false;
             const int32_t py = alive ? quant(st.p[0], inv_q) : 0;
             const int32_t pz = alive ? quant(st.p[1], inv_q) : 0;
-            put(w, S_DY, j, zigzag(cy - py), cy - py);
-            put(w, S_DZ, j, zigzag(cz - pz), cz - pz);
+            symbol(s_dy, S_DY, j, zigzag(cy - py), cy - py);
+            symbol(s_dz, S_DZ, j, zigzag(cz - pz), cz - pz);
+            s_q = (s_q >> 8) | ((uint64_t)(uint8_t)charge_code(qc, cbits) << 56);
             if (alive) {
                 kupdate(st, (float)cy / inv_q, (float)cz / inv_q, prm.sigma_y2, prm.sigma_z2);
                 x = xr;
             }
-            w.sym[S_Q][j] = (uint8_t)charge_code(qc, cbits);
+            if (((j - a) & 7) == 7) {
+                memcpy(w.sym[S_ROW] + j - 7, &s_row, 8);
+                memcpy(w.sym[S_DY] + j - 7, &s_dy, 8);
+                memcpy(w.sym[S_DZ] + j - 7, &s_dz, 8);
+                memcpy(w.sym[S_Q] + j - 7, &s_q, 8);
+            }
+        }
+        // the last (b - a) % 8 of each, the oldest the lowest of their bytes
+        for (int n = b > a ? (b - a) & 7 : 0; n > 0; --n) {
+            const int sh = 8 * (8 - n);
+            w.sym[S_ROW][b - n] = (uint8_t)(s_row >> sh);
+            w.sym[S_DY][b - n] = (uint8_t)(s_dy >> sh);
+            w.sym[S_DZ][b - n] = (uint8_t)(s_dz >> sh);
+            w.sym[S_Q][b - n] = (uint8_t)(s_q >> sh);
         }
     }
 }
@@ -302,17 +330,40 @@ __global__ void k_cz_counts(const int32_t* __restrict__ off, const int64_t* __re
     for (int k = 0; k < kStreams; ++k) w.counts[3 + k] = n[k];
 }
 
-// histogram of stream blockIdx.y
+// A tile of the symbols of a stream: 8 symbols a thread in one load (symbols
+// past the size read as zero).
+__device__ __forceinline__ uint64_t tile_symbols(const CmpWs& w, int k, int64_t tile, int64_t n)
+{
+    const int64_t i = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    if (i >= n) return 0;
+    const uint64_t v = *reinterpret_cast<const uint64_t*>(w.sym[k] + i);
+    return n - i >= kScanItems ? v : v & ((1ull << (8 * (n - i))) - 1ull);
+}
+
+__device__ __forceinline__ bool has_escapes(int k) { return k != S_Q && k != S_UYL; }
+
+// histogram of stream blockIdx.y and the escapes of each of its tiles
 __global__ __launch_bounds__(kBlock) void k_cz_hist(CmpWs w)
 {
     __shared__ uint32_t h[256];
+    __shared__ int red[kBlock / kWave];
     const int k = blockIdx.y;
     for (int i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
     __syncthreads();
     const int64_t n = w.counts[3 + k];
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&h[w.sym[k][i]], 1u);
+    for (int64_t t = blockIdx.x; t * kScanTile < n; t += gridDim.x) {
+        const uint64_t v = tile_symbols(w, k, t, n);
+        const int64_t i = t * kScanTile + (int64_t)threadIdx.x * kScanItems;
+        int esc = 0;
+#pragma unroll
+        for (int b = 0; b < kScanItems; ++b) {
+            const uint32_t sy = (uint32_t)(v >> (8 * b)) & 255u;
+            if (i + b < n) atomicAdd(&h[sy], 1u);
+            esc += sy == 255u;
+        }
+        const int tot = block_sum(has_escapes(k) ? esc : 0, red);
+        if (threadIdx.x == 0) w.ecnt[k * w.etiles + t] = tot;
+    }
     __syncthreads();
     for (int i = threadIdx.x; i < 256; i += blockDim.x)
         if (h[i]) atomicAdd(&w.hist[k * 256 + i], h[i]);
@@ -321,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_cz_hist(CmpWs w)
 // counts -> 12-bit frequencies (the reading's normalisation: floor of the
 // share, at least 1, then the sum is brought to 2^12 one unit at a time, down
 // on the largest frequency above 1, up on the largest count, ties to the
-// lower symbol); one thread per stream
+// lower symbol), and the places of the escapes; one block per stream
 __global__ __launch_bounds__(kBlock) void k_cz_norm(CmpWs w)
 {
     // one thread per symbol.  The rule, decrementing the largest frequency
@@ -377,6 +428,18 @@ __global__ __launch_bounds__(kBlock) void k_cz_norm(CmpWs w)
         if (key == best) fi += (uint32_t)(kProbScale - sum);
     }
     w.freq[k * 256 + i] = fi;
+    // the escapes before every tile, and all of them
+    const int64_t nt = (w.counts[3 + k] + kScanTile - 1) / kScanTile;
+    uint64_t carry = 0;
+    for (int64_t t0 = 0; t0 < nt; t0 += kBlock) {
+        const int64_t t = t0 + i;
+        const uint64_t v = t < nt ? (uint64_t)w.ecnt[k * w.etiles + t] : 0ull;
+        uint64_t all;
+        const uint64_t ex = block_excl_scan<uint64_t>(v, red, &all);
+        if (t < nt) w.ecnt[k * w.etiles + t] = (int32_t)(carry + ex);
+        carry += all;
+    }
+    if (i == 0) w.eoff[k] = (int64_t)carry;
     uint64_t tot;
     const uint64_t c = block_excl_scan<uint64_t>(fi, red, &tot);
     w.cum[k * 256 + i] = (uint32_t)c;
@@ -394,8 +457,13 @@ __device__ __forceinline__ uint32_t byte_of(const uint4& v, int b)
     return (word >> (8 * (b & 3))) & 255u;
 }
 
-// one thread per (chunk, stream): rANS encode backwards; the bytes end at the
-// end of the chunk's slot
+// One thread per (chunk, stream): rANS encode backwards; the bytes end at the
+// end of the chunk's slot.  Bound by the serial chain of a chunk: 21 VALU
+// instructions a symbol, some of them quarter rate, and a wait per kAhead
+// blocks.  Central event, chunks of 4096 symbols: 430 us with a wait per
+// block, four tables read by word and a conditional store per symbol, 330
+// now; 16 or 4 chunks to a wave instead of 64 are no faster.
+constexpr int kAhead = 8;
 __global__ __launch_bounds__(kBlock) void k_cz_encode(CmpWs w, int chunk)
 {
     // Per symbol: the renormalisation bound, and the quotient by its
@@ -404,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void k_cz_encode(CmpWs w, int chunk)
     // is below 2^31, and with l = ceil(log2 f), M = ceil(2^(31 + l) / f) < 2^32,
     // x / f = (x M) >> (31 + l) = hi32(2x M) >> l for every x < 2^31.  The new
     // state (x / f) 2^12 + x mod f + c equals x + c + (x / f) (2^12 - f).
-    __shared__ uint32_t xm_l[256], m_l[256], pk_l[256], c_l[256];
+    __shared__ uint4 tab[256];
     const int k = blockIdx.y;
     {
         const uint32_t f = w.freq[k * 256 + threadIdx.x];
@@ -413,10 +481,8 @@ __global__ __launch_bounds__(kBlock) void k_cz_encode(CmpWs w, int chunk)
             l = f > 1 ? 32u - (uint32_t)__clz(f - 1u) : 0u;
             mm = (uint32_t)((((uint64_t)1 << (31 + l)) + f - 1) / f);
         }
-        xm_l[threadIdx.x] = ((kRansL >> kProbBits) << 8) * f;
-        m_l[threadIdx.x] = mm;
-        pk_l[threadIdx.x] = (kProbScale - f) | (l << 16);
-        c_l[threadIdx.x] = w.cum[k * 256 + threadIdx.x];
+        tab[threadIdx.x] = make_uint4(((kRansL >> kProbBits) << 8) * f, mm,
+                                      (kProbScale - f) | (l << 16), w.cum[k * 256 + threadIdx.x]);
     }
     __syncthreads();
     const int64_t n = w.counts[3 + k];
@@ -426,71 +492,89 @@ __global__ __launch_bounds__(kBlock) void k_cz_encode(CmpWs w, int chunk)
     const uint8_t* s = w.sym[k];
     const int64_t a = j * chunk, e = a + chunk < n ? a + chunk : n;
     // bytes go backwards from the end of the chunk's slot (256-byte aligned),
-    // gathered into words (the first of four at the top, the highest address)
-    uint8_t* end = w.cbuf + ((int64_t)k * w.chunk_cap + j) * w.slot + w.slot;
-    uint32_t m = 0;
+    // gathered into words (the first of four at the top, the highest
+    // address).  A word is stored every two symbols (at most four bytes and
+    // three left over), whole or not: what is not yet whole is stored again
+    // one time later, at the same place, and the slot has room for it.
+    uint32_t* word = reinterpret_cast<uint32_t*>(w.cbuf + ((int64_t)k * w.chunk_cap + j) * w.slot +
+                                                 w.slot) - 1;
+    uint32_t* const first = word;
+    uint32_t pend = 0;                 // bytes in acc, the oldest the highest
     uint64_t acc = 0;
     uint32_t x = kRansL;
-    // nb (0, 1 or 2) bytes, the first in the higher byte of v
+    // nb (0, 1 or 2) low bytes of v, the lowest first
     auto emit = [&](uint32_t v, uint32_t nb) {
-        acc = (acc << (8 * nb)) | (v & ((1u << (8 * nb)) - 1u));
-        m += nb;
-        if ((m & 3u) < nb) *reinterpret_cast<uint32_t*>(end - (m & ~3u)) = (uint32_t)(acc >> (8 * (m & 3u)));
+        const uint32_t sel = nb == 2 ? 0x0c0c0001u : nb == 1 ? 0x0c0c0c00u : 0x0c0c0c0cu;
+        acc = (acc << (8 * nb)) | __builtin_amdgcn_perm(0u, v, sel);
+        pend += nb;
+    };
+    auto flush = [&]() {
+        // pend <= 7: the four oldest bytes, or all of them at the top
+        const uint32_t up = (uint32_t)acc << ((32u - 8u * pend) & 31u);
+        *word = pend >= 4 ? (uint32_t)(acc >> (8 * pend - 32u)) : up;
+        word -= pend >> 2;
+        pend &= 3u;
     };
     // renormalise (x < 2^31 and the bound is at least 2^19: at most two
     // bytes, the low one first), then the state step
-    auto code = [&](uint32_t xm, uint32_t mm, uint32_t pk, uint32_t c) {
+    auto code = [&](const uint4& e) {
+        const uint32_t xm = e.x, mm = e.y, pk = e.z, c = e.w;
         const uint32_t nb = (x >= xm ? 1u : 0u) + ((x >> 8) >= xm ? 1u : 0u);
-        emit(nb == 2 ? ((x & 255u) << 8) | ((x >> 8) & 255u) : x & 255u, nb);
+        emit(x, nb);
         x >>= 8 * nb;
+        // x < 2^19 f here: the quotient fits 24 bits
         const uint32_t q = __umulhi(x << 1, mm) >> (pk >> 16);
-        x += c + q * (pk & 0xFFFFu);
+        x += c + __umul24(q, pk & 0xFFFFu);
     };
-    auto code_sym = [&](uint32_t sy) { code(xm_l[sy], m_l[sy], pk_l[sy], c_l[sy]); };
+    auto code_sym = [&](uint32_t sy) {
+        code(tab[sy]);
+        flush();
+    };
     int64_t i = e;
     if ((a & 15) == 0) {          // 16-byte blocks (chunk sizes that are multiples of 16)
-        // the ragged tail first (symbols past the last multiple of 16)
+        // the ragged tail first (symbols past the last multiple of 16), then
+        // kAhead blocks at a time: the wait for the next ones is also one for
+        // the stores of these (both count down one counter)
         const int64_t e16 = a + (e - a) / 16 * 16;
         while (i > e16) code_sym(s[--i]);
-        uint4 nxt = make_uint4(0, 0, 0, 0);
-        if (i > a) nxt = load16(s + i - 16);
+        uint4 nxt[kAhead];
+        auto fetch = [&](int64_t at) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+                if (at - 16 * q > a) nxt[q] = load16(s + at - 16 * q - 16);
+        };
+        fetch(i);
         while (i > a) {
-            const uint4 cur = nxt;
-            if (i - 16 > a) nxt = load16(s + i - 32);     // the next block, in flight meanwhile
-            // the block's table entries first, then the dependent steps
-            uint32_t txm[16], tm[16], tpk[16], tc[16];
+            uint4 cur[kAhead];
 #pragma unroll
-            for (int b = 0; b < 16; ++b) {
-                const uint32_t sy = byte_of(cur, b);
-                txm[b] = xm_l[sy];
-                tm[b] = m_l[sy];
-                tpk[b] = pk_l[sy];
-                tc[b] = c_l[sy];
+            for (int q = 0; q < kAhead; ++q) cur[q] = nxt[q];
+            fetch(i - 16 * kAhead);
+#pragma unroll 1
+            for (int q = 0; q < kAhead && i > a; ++q) {
+                // the block's table entries first, then the dependent steps
+                uint4 t[16];
+#pragma unroll
+                for (int b = 0; b < 16; ++b) t[b] = tab[byte_of(cur[0], b)];
+#pragma unroll
+                for (int b = 15; b >= 0; --b) {
+                    code(t[b]);
+                    if ((b & 1) == 0) flush();
+                }
+                i -= 16;
+#pragma unroll
+                for (int u = 0; u + 1 < kAhead; ++u) cur[u] = cur[u + 1];
             }
-#pragma unroll
-            for (int b = 15; b >= 0; --b) code(txm[b], tm[b], tpk[b], tc[b]);
-            i -= 16;
         }
     }
     while (i > a) code_sym(s[--i]);
-    // the final state, low byte first
-    emit(((x & 255u) << 8) | ((x >> 8) & 255u), 2);
-    emit(((x >> 16) & 255u) << 8 | (x >> 24), 2);
-    // the bytes of a last, partial word
-    const uint32_t p = m & 3u;
-    for (uint32_t t = 0; t < p; ++t)
-        *(end - 1 - (m - p) - t) = (uint8_t)(acc >> (8 * (p - 1 - t)));
-    w.csize[(int64_t)k * w.chunk_cap + j] = m;
-}
-
-// escape flags of stream k over its capacity (zero past its size)
-__global__ __launch_bounds__(kBlock) void k_cz_eflag(CmpWs w, int k)
-{
-    const int64_t n = w.counts[3 + k];
-    const bool esc_ok = k != S_Q && k != S_UYL;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < w.cap[k];
-         i += (int64_t)gridDim.x * blockDim.x)
-        w.eflag[i] = (esc_ok && i < n && w.sym[k][i] == 255) ? 1 : 0;
+    // the final state, low byte first (three bytes may be pending: a word at
+    // a time), and the bytes of a last, partial word
+    emit(x & 0xFFFFu, 2);
+    flush();
+    emit(x >> 16, 2);
+    flush();
+    flush();
+    w.csize[(int64_t)k * w.chunk_cap + j] = (uint32_t)(first - word) * 4u + pend;
 }
 
 __device__ __forceinline__ void put32(uint8_t* out, int64_t at, uint32_t v)
@@ -615,18 +699,34 @@ __global__ __launch_bounds__(kBlock) void k_cz_copy_chunks(CmpWs w, int chunk,
     }
 }
 
-// escapes of stream k in symbol order (eflag holds the exclusive scan of the
-// flags)
-__global__ __launch_bounds__(kBlock) void k_cz_copy_esc(CmpWs w, int k, uint8_t* __restrict__ out)
+// escapes of stream blockIdx.y in symbol order.  (Flagged and scanned stream
+// by stream over the capacities, twice, they were 63 of the 78 launches and
+// 360 us of a central event's 1115.)
+__global__ __launch_bounds__(kBlock) void k_cz_copy_esc(CmpWs w, uint8_t* __restrict__ out)
 {
+    __shared__ int red[kBlock / kWave];
     if (!w.lay[3 * kStreams + 1]) return;
+    const int k = blockIdx.y;
+    if (!has_escapes(k)) return;
     const int64_t n = w.counts[3 + k];
     const int64_t base = w.lay[3 * k + 1];
-    const bool esc_ok = k != S_Q && k != S_UYL;
-    if (!esc_ok) return;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        if (w.sym[k][i] == 255) put32(out, base + 4 * (int64_t)w.eflag[i], (uint32_t)w.esc[k][i]);
+    for (int64_t t = blockIdx.x; t * kScanTile < n; t += gridDim.x) {
+        const int64_t e0 = w.ecnt[k * w.etiles + t];
+        const int64_t e1 = (t + 1) * kScanTile < n ? (int64_t)w.ecnt[k * w.etiles + t + 1]
+                                                   : w.eoff[k];
+        if (e0 == e1) continue;
+        const uint64_t v = tile_symbols(w, k, t, n);
+        int esc = 0;
+#pragma unroll
+        for (int b = 0; b < kScanItems; ++b) esc += ((v >> (8 * b)) & 255u) == 255u;
+        int tot;
+        int64_t at = e0 + block_excl_scan(esc, red, &tot);
+        const int64_t i = t * kScanTile + (int64_t)threadIdx.x * kScanItems;
+#pragma unroll
+        for (int b = 0; b < kScanItems; ++b)
+            if (((v >> (8 * b)) & 255u) == 255u)
+                put32(out, base + 4 * at++, (uint32_t)w.esc[k][i + b]);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_cz_copy_hdr(CmpWs w, uint8_t* __restrict__ out)
@@ -670,7 +770,8 @@ size_t layout_cmp(const tpc_problem* p, int64_t track_cap, int64_t hit_cap, int 
         w->sym[k] = (uint8_t*)take((size_t)cap[k]);
         w->esc[k] = (int32_t*)take(4 * (size_t)cap[k]);
     }
-    w->eflag = (int32_t*)take(4 * (size_t)(maxcap + 1));
+    w->etiles = ceil_div(maxcap, kScanTile);
+    w->ecnt = (int32_t*)take(4 * (size_t)kStreams * (size_t)w->etiles);
     w->rowcnt = (int32_t*)take(4 * (size_t)(nrs + 1));
     w->hdr = (uint8_t*)take(16 * (size_t)track_cap);
     w->hist = (uint32_t*)take(4 * kStreams * 256);
@@ -747,7 +848,8 @@ int tpc_compress_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_clust
                    st, (const int32_t*)tracks.off, (const int32_t*)tracks.hits, d_n_tracks, tcap,
                    w);
         TPC_LAUNCH(tpc::k_cz_tracks, dim3(tpc::grid_for(tcap)), dim3(tpc::kBlock), 0, st,
-                   h_prob->d_row_x, h_prob->params, clusters.row, clusters.y, clusters.z, charge,
+                   h_prob->d_row_x, n_rows, h_prob->params, clusters.row, clusters.y, clusters.z,
+                   charge,
                    (const int32_t*)tracks.off, (const int32_t*)tracks.hits,
                    (const uint8_t*)tracks.hit_row, (const float*)tracks.hit_y,
                    (const float*)tracks.hit_z, (const int32_t*)tracks.tracklet,
@@ -762,31 +864,18 @@ int tpc_compress_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_clust
                h_prob->d_sectors, n_sec, n_rows, (const int32_t*)grid.bin_start,
                (const int32_t*)grid.id, clusters.y, clusters.z, charge,
                (const int32_t*)tracks.off, d_n_tracks, tcap, inv_q, cp.cbits, w);
-    TPC_LAUNCH(tpc::k_cz_hist, dim3(256, tpc::kStreams), dim3(tpc::kBlock), 0, st, w);
+    const unsigned tiles = tpc::grid_for_block(w.etiles, 1, 256);
+    TPC_LAUNCH(tpc::k_cz_hist, dim3(tiles, tpc::kStreams), dim3(tpc::kBlock), 0, st, w);
     TPC_LAUNCH(tpc::k_cz_norm, dim3(tpc::kStreams), dim3(tpc::kBlock), 0, st, w);
     TPC_LAUNCH(tpc::k_cz_encode,
                dim3((unsigned)tpc::ceil_div(w.chunk_cap, tpc::kBlock), tpc::kStreams),
                dim3(tpc::kBlock), 0, st, w, (int)cp.chunk);
-    // escape counts, the layout and header, then the chunk bytes, the
-    // escapes in order (flags scanned again per stream) and the headers
-    for (int k = 0; k < tpc::kStreams; ++k) {
-        TPC_LAUNCH(tpc::k_cz_eflag, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st, w,
-                   k);
-        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, w.eoff + k,
-                                  w.partials, st);
-    }
+    // the layout and header, then the chunk bytes, the escapes and the headers
     TPC_LAUNCH(tpc::k_cz_layout, dim3(1), dim3(tpc::kBlock), 0, st, w, (int)cp.cbits, (int)cp.qbits,
                (int)cp.chunk, n_sec, n_rows, n, out, out_cap, d_size);
     TPC_LAUNCH(tpc::k_cz_copy_chunks, dim3(1024, tpc::kStreams), dim3(tpc::kBlock), 0, st, w,
                (int)cp.chunk, out);
-    for (int k = 0; k < tpc::kStreams; ++k) {
-        TPC_LAUNCH(tpc::k_cz_eflag, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st, w,
-                   k);
-        tpc::launch_scan<int32_t>(w.eflag, w.eflag, w.cap[k], false, nullptr,
-                                  w.partials, st);
-        TPC_LAUNCH(tpc::k_cz_copy_esc, dim3(tpc::grid_for(w.cap[k])), dim3(tpc::kBlock), 0, st,
-                   w, k, out);
-    }
+    TPC_LAUNCH(tpc::k_cz_copy_esc, dim3(tiles, tpc::kStreams), dim3(tpc::kBlock), 0, st, w, out);
     TPC_LAUNCH(tpc::k_cz_copy_hdr, dim3(tpc::grid_for(16 * (tcap > 0 ? tcap : 1))),
                dim3(tpc::kBlock), 0, st, w, out);
     return hipGetLastError() == hipSuccess ? TPC_OK : TPC_ERR_HIP;
