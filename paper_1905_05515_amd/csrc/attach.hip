@@ -4,14 +4,12 @@
 // them; clusters in the tubes of good tracks are protected; attached or
 // adjacent clusters that are not protected are removed.
 //
-// One thread per track walks its rows: the track state (the tracklet's,
-// at the plane of its innermost fitted row) is transported outwards row by
-// row with the tracklet construction's transport, and on every row from the
-// track's first to its last hit the grid bins covering the tube's cross
-// section are scanned; the exact test dy*dy + dz*dz <= radius^2 decides.
-// The working flags are kept by grid position, so that a candidate's flags
-// load with its coordinates; the bin bounds of a row are loaded before the
-// transport to the next row is computed, which hides their latency.
+// The track state (the tracklet's, at the plane of its innermost fitted row)
+// is transported outwards row by row with the tracklet construction's
+// transport, and on every row from the track's first to its last hit the grid
+// bins covering the tube's cross section are scanned; the exact test
+// dy*dy + dz*dz <= radius^2 decides.  The working flags are kept by grid
+// position, so that a candidate's flags load with its coordinates.
 // The adjacent track of a cluster is a 64-bit atomic max over tubes of the
 // key (~bits(|q/pT|), ~track): for non-negative floats the bit pattern
 // orders like the value, so the largest key is the least |q/pT| and, among
@@ -83,75 +81,92 @@ __global__ __launch_bounds__(kWave) void k_attach_own(
         }
 }
 
-// One thread per track: its tube, row by row.
-__global__ __launch_bounds__(kWave) void k_attach_tube(
+// The tubes of kTubeTracks tracks a block: first one lane per track carries
+// its state from row to row (nothing is measured, so this chain, some 60
+// instructions a row, is the only serial one) and leaves the tube's centre in
+// every row in LDS, then every (track, row) is searched by a lane of its own.
+// Bound by the search's two dependent loads (218 MB fetched) and the atomics,
+// 512 lanes a block in flight.  One lane per track searching its rows one
+// after the other waited for them 71% of its time: 477 us for the 16,800
+// tracks of a central event, now 190 (16 tracks and 256 lanes: 186; 16 and
+// 512: 209; 64 and 1024: 213).
+constexpr int kTubeTracks = 32;
+constexpr int kTubeBlock = 512;
+
+__global__ __launch_bounds__(kTubeBlock) void k_attach_tube(
     const tpc_sector* __restrict__ sec, int n_sec, int n_rows, const float* __restrict__ row_x,
     tpc_params prm, const uint8_t* __restrict__ row, const int32_t* __restrict__ bin_start,
-    const float* __restrict__ yg, const float* __restrict__ zg, const int32_t* __restrict__ idg,
+    const float* __restrict__ yg, const float* __restrict__ zg,
     const int32_t* __restrict__ trk_off, const int32_t* __restrict__ trk_hits,
     const int32_t* __restrict__ trk_tracklet, const float* __restrict__ t_par,
     const int32_t* __restrict__ t_rin, const int64_t* __restrict__ d_n_tracks, int64_t trk_cap,
     float radius, float r2, float w_good, AttachWs w)
 {
+    extern __shared__ float2 centre[];        // [n_rows][kTubeTracks]
     __shared__ float xs[256];
+    __shared__ int sector_[kTubeTracks], from_[kTubeTracks], to_[kTubeTracks];
+    __shared__ float absw_[kTubeTracks];
     for (int i = threadIdx.x; i < n_rows; i += blockDim.x) xs[i] = row_x[i];
-    __syncthreads();
     const int64_t nt = track_count(d_n_tracks, trk_cap);
     // tube cross section widened before taking bins: a rounding difference
     // at its edge never drops a cluster, the exact test decides
     const float hw = radius * TPC_WIDEN + 0.01f;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < nt;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t a = trk_off[k], b = trk_off[k + 1];
-        if (b <= a) continue;
-        const int32_t c0 = trk_hits[a];
-        const int r_first = row[c0], r_last = row[trk_hits[b - 1]];
-        const tpc_sector s = sec[find_sector(sec, n_sec, c0)];
-        const int32_t t = trk_tracklet[k];
-        KState st;
+    for (int64_t k0 = blockIdx.x * (int64_t)kTubeTracks; k0 < nt;
+         k0 += (int64_t)gridDim.x * kTubeTracks) {
+        __syncthreads();
+        if (threadIdx.x < kTubeTracks) {
+            const int64_t k = k0 + threadIdx.x;
+            const int32_t a = k < nt ? trk_off[k] : 0, b = k < nt ? trk_off[k + 1] : 0;
+            int from = 0, to = -1;            // rows with a tube
+            if (b > a) {
+                const int32_t c0 = trk_hits[a];
+                const int r_first = row[c0], r_last = row[trk_hits[b - 1]];
+                const int32_t t = trk_tracklet[k];
+                KState st;
 #pragma unroll
-        for (int i = 0; i < 5; ++i) st.p[i] = t_par[(int64_t)t * 5 + i];
+                for (int i = 0; i < 5; ++i) st.p[i] = t_par[(int64_t)t * 5 + i];
 #pragma unroll
-        for (int i = 0; i < 15; ++i) st.C[i] = 0.0f;
-        const float aw = fabsf(st.p[4]);
+                for (int i = 0; i < 15; ++i) st.C[i] = 0.0f;
+                sector_[threadIdx.x] = find_sector(sec, n_sec, c0);
+                absw_[threadIdx.x] = fabsf(st.p[4]);
+                const int r0 = t_rin[t];
+                from = r0 > r_first ? r0 : r_first;
+                bool alive = true;
+                for (int r = r0; alive && r <= r_last && r < n_rows; ++r) {
+                    centre[r * kTubeTracks + threadIdx.x] = make_float2(st.p[0], st.p[1]);
+                    to = r;
+                    if (r < r_last && r + 1 < n_rows)
+                        alive = propagate(st, xs[r + 1] - xs[r], prm.curv, prm.s_max);
+                }
+            }
+            from_[threadIdx.x] = from;
+            to_[threadIdx.x] = to;
+        }
+        __syncthreads();
+        const int i = threadIdx.x % kTubeTracks;
+        const int r_to = to_[i];
+        int r = from_[i] + (int)(threadIdx.x / kTubeTracks);
+        if (r > r_to) continue;
+        const tpc_sector s = sec[sector_[i]];
+        const float aw = absw_[i];
         const bool good = aw <= w_good;
         const unsigned long long key =
             ((unsigned long long)(0xFFFFFFFFu - __float_as_uint(aw)) << 32) |
-            (unsigned long long)(0xFFFFFFFFu - (uint32_t)k);
-        const int r0 = t_rin[t];
-        bool alive = true;
-        for (int r = r0; alive && r <= r_last && r < n_rows; ++r) {
-            const float py = st.p[0], pz = st.p[1];
-            const bool in_tube_rows = r >= r_first;
-            int iy0 = 0, iy1 = -1, iz0 = 0, iz1 = -1;
-            int lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
-            if (in_tube_rows) {
-                iy0 = bin_of(py - hw, s.y0, s.inv_by, s.nby);
-                iy1 = bin_of(py + hw, s.y0, s.inv_by, s.nby);
-                iz0 = bin_of(pz - hw, s.z0, s.inv_bz, s.nbz);
-                iz1 = bin_of(pz + hw, s.z0, s.inv_bz, s.nbz);
-                const int g = s.bin_base + (r * s.nbz + iz0) * s.nby;
-                lo0 = bin_start[g + iy0];
-                hi0 = bin_start[g + iy1 + 1];
-                if (iz0 + 1 <= iz1) {
+            (unsigned long long)(0xFFFFFFFFu - (uint32_t)(k0 + i));
+        for (; r <= r_to; r += kTubeBlock / kTubeTracks) {
+            const float2 c = centre[r * kTubeTracks + i];
+            const float py = c.x, pz = c.y;
+            const int iy0 = bin_of(py - hw, s.y0, s.inv_by, s.nby);
+            const int iy1 = bin_of(py + hw, s.y0, s.inv_by, s.nby);
+            const int iz0 = bin_of(pz - hw, s.z0, s.inv_bz, s.nbz);
+            const int iz1 = bin_of(pz + hw, s.z0, s.inv_bz, s.nbz);
+            for (int iz = iz0; iz <= iz1; iz += 2) {
+                const int g = s.bin_base + (r * s.nbz + iz) * s.nby;
+                const int lo0 = bin_start[g + iy0], hi0 = bin_start[g + iy1 + 1];
+                int lo1 = 0, hi1 = 0;
+                if (iz + 1 <= iz1) {
                     lo1 = bin_start[g + s.nby + iy0];
                     hi1 = bin_start[g + s.nby + iy1 + 1];
-                }
-            }
-            // the next row's transport while the bounds load
-            if (r < r_last && r + 1 < n_rows)
-                alive = propagate(st, xs[r + 1] - xs[r], prm.curv, prm.s_max);
-            if (!in_tube_rows) continue;
-            for (int iz = iz0; iz <= iz1; iz += 2) {
-                if (iz > iz0) {
-                    const int g = s.bin_base + (r * s.nbz + iz) * s.nby;
-                    lo0 = bin_start[g + iy0];
-                    hi0 = bin_start[g + iy1 + 1];
-                    lo1 = hi1 = 0;
-                    if (iz + 1 <= iz1) {
-                        lo1 = bin_start[g + s.nby + iy0];
-                        hi1 = bin_start[g + s.nby + iy1 + 1];
-                    }
                 }
                 // the candidates of both z rows as one stream, kCandBatch
                 // loads at a time
@@ -260,10 +275,11 @@ int tpc_attach_clusters(tpc_context* ctx, const tpc_problem* h_prob, tpc_cluster
                dim3(tpc::kWave), 0, st, (const int32_t*)tracks.off, (const int32_t*)tracks.hits, d_n_tracks,
                tracks.capacity, track, w);
     TPC_LAUNCH(tpc::k_attach_tube,
-               dim3(tpc::grid_for_block(tracks.capacity, tpc::kWave, 65536)), dim3(tpc::kWave),
-               0, st, h_prob->d_sectors, h_prob->n_sectors, h_prob->n_rows, h_prob->d_row_x,
+               dim3(tpc::grid_for_block(tracks.capacity, tpc::kTubeTracks, 65536)),
+               dim3(tpc::kTubeBlock), sizeof(float2) * tpc::kTubeTracks * h_prob->n_rows, st,
+               h_prob->d_sectors, h_prob->n_sectors, h_prob->n_rows, h_prob->d_row_x,
                h_prob->params, in.row, (const int32_t*)grid.bin_start, (const float*)grid.y,
-               (const float*)grid.z, (const int32_t*)grid.id, (const int32_t*)tracks.off,
+               (const float*)grid.z, (const int32_t*)tracks.off,
                (const int32_t*)tracks.hits, (const int32_t*)tracks.tracklet,
                (const float*)tracklets.par, (const int32_t*)tracklets.row_inner, d_n_tracks,
                tracks.capacity, radius, r2, w_good, w);
