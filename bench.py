@@ -677,6 +677,8 @@ def roofline(name, avg_ms, st, n_cl, n_trk_hits):
         "k_grid_rows_scatter": 21,
         # per-row bin sort: read y, z (8 B), write slot and bin (8 B)
         "k_grid_bins": 16,
+        # large buckets: read y, z, id (12 B), write y, z, id, gsr (16 B)
+        "k_grid_big": 28,
         # final place: read slot, bin, id, y, z (20 B), write y, z, id, gsr (16 B)
         "k_grid_place": 36,
         # reads y, z, gsr (12 B) writes up0, down0 (8 B)
@@ -701,7 +703,8 @@ def roofline(name, avg_ms, st, n_cl, n_trk_hits):
                 "flops_per_launch": fl, "propagations": st["n_propagations"],
                 "updates": st["n_updates"], "candidates": st["n_candidates"]}
     if base in ("k_refit_fwd", "k_refit_adj"):
-        per_hit = 4 + 9 + (80 if name == "k_refit_fwd" else 88)
+        # packed hit, every second state a checkpoint (two gradients)
+        per_hit = 9 + (40 if base == "k_refit_fwd" else 48)
         b = per_hit * n_trk_hits
         gbs = b / sec / 1e9
         return {"kernel": name, "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
@@ -716,8 +719,8 @@ def roofline(name, avg_ms, st, n_cl, n_trk_hits):
 # unchanged)
 KERNEL_SOURCES = {
     "k_tracklets": ["tracklets.hip", "tracklet_dev.hpp", "exact_fp32.hpp", "tpc_internal.hpp"],
-    "k_refit_fwd": ["refit.hip", "tpc_internal.hpp"],
-    "k_refit_adj": ["refit.hip", "tpc_internal.hpp"],
+    "k_refit_fwd": ["refit.hip", "exact_fp32.hpp", "tpc_internal.hpp"],
+    "k_refit_adj": ["refit.hip", "exact_fp32.hpp", "tpc_internal.hpp"],
     # every kernel that tpc_build_grid and tpc_find_neighbours launch
     "grid_to_starts": ["grid.hip", "grid_dev.hpp", "neighbours.hip", "seed_dev.hpp",
                        "block_dev.hpp", "util.hip", "tpc_internal.hpp"],
