@@ -718,7 +718,8 @@ def roofline(name, avg_ms, st, n_cl, n_trk_hits):
 # sources a kernel is built from (a counter summary applies while they are
 # unchanged)
 KERNEL_SOURCES = {
-    "k_tracklets": ["tracklets.hip", "tracklet_dev.hpp", "exact_fp32.hpp", "tpc_internal.hpp"],
+    "k_tracklets": ["tracklets.hip", "tracklet_dev.hpp", "exact_fp32.hpp", "block_dev.hpp",
+                    "tpc_internal.hpp"],
     "k_refit_fwd": ["refit.hip", "exact_fp32.hpp", "tpc_internal.hpp"],
     "k_refit_adj": ["refit.hip", "exact_fp32.hpp", "tpc_internal.hpp"],
     # every kernel that tpc_build_grid and tpc_find_neighbours launch

@@ -86,12 +86,12 @@ __global__ __launch_bounds__(kWave) void k_attach_own(
 // instructions a row, is the only serial one) and leaves the tube's centre in
 // every row in LDS, then every (track, row) is searched by a lane of its own.
 // Bound by the search's two dependent loads (218 MB fetched) and the atomics,
-// 512 lanes a block in flight.  One lane per track searching its rows one
+// 256 lanes a block in flight.  One lane per track searching its rows one
 // after the other waited for them 71% of its time: 477 us for the 16,800
-// tracks of a central event, now 190 (16 tracks and 256 lanes: 186; 16 and
-// 512: 209; 64 and 1024: 213).
-constexpr int kTubeTracks = 32;
-constexpr int kTubeBlock = 512;
+// tracks of a central event, now 186 (16 tracks and 512 lanes: 209; 32 and
+// 512: 190; 64 and 1024: 213).
+constexpr int kTubeTracks = 16;
+constexpr int kTubeBlock = 256;
 
 __global__ __launch_bounds__(kTubeBlock) void k_attach_tube(
     const tpc_sector* __restrict__ sec, int n_sec, int n_rows, const float* __restrict__ row_x,

@@ -1,4 +1,4 @@
-"""Tubes are searched 32 tracks to a block, a lane per track and row: track
+"""Tubes are searched 16 tracks to a block, a lane per track and row: track
 counts around a block and tubes from none to every row, against the oracle
 cluster by cluster."""
 import numpy as np
@@ -11,7 +11,7 @@ from test_gpu_attach import _check
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_tracks", [1, 20, 34, 36, 70])
+@pytest.mark.parametrize("n_tracks", [1, 15, 18, 20, 34, 36, 70])
 @pytest.mark.parametrize("radius", [0.05, 1.5, 40.0])
 def test_tubes(n_tracks, radius):
     ev = synth.make_config1(n_tracks=n_tracks)
