@@ -246,7 +246,8 @@ void timer_begin(const char* name, hipStream_t st)
 {
     KernelTimer* t = t_timer;
     if (!t || capturing(st)) return;
-    for (const char* c = name; *c; ++c)      // drop namespace qualifiers
+    if (*name == '(') ++name;
+    for (const char* c = name; *c && *c != '<'; ++c)      // drop namespace qualifiers
         if (c[0] == ':' && c[1] == ':') name = c + 2;
     hipEvent_t e = t->take();
     if (!e || hipEventRecord(e, st) != hipSuccess) return;
