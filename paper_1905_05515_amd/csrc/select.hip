@@ -47,14 +47,17 @@ __global__ __launch_bounds__(kBlock) void k_sel_chunk(
 // Row form for big sectors.  One block per (sector, pad row) keeps the
 // ownership keys of the row's grid positions in LDS (in slices of 64 KB of
 // keys when the row has more), reads the row's entry of
-// every tracklet of the sector, claims with a 64-bit LDS atomic max, writes
-// the keys out and records which tracklets keep their hit on the row as one
-// bit per tracklet (kbits[row][t / 64], bit t % 64).  A second kernel sums
-// the bits of every row chunk into the kept counts.  No device-wide atomic
-// per hit: on a continuous read-out slice (3.4M tracklets over 36 sectors
-// of 1.9M clusters) the tracklet-parallel form with one 64-bit device atomic
-// per hit took 11 + 3.5 ms, this form with 64-bit keys in slices of 8192
-// positions (two per row there) 5.1 + 0.7 ms.
+// every tracklet of the sector, claims with an LDS atomic max and records
+// which tracklets keep their hit on the row as one bit per tracklet
+// (kbits[row][t / 64], bit t % 64), which is all that is read of it later.  A
+// second kernel sums the bits of every row chunk into the kept counts.  No
+// device-wide atomic per hit: on a continuous read-out slice (3.4M tracklets
+// over 36 sectors of 1.9M clusters) the tracklet-parallel form with one 64-bit
+// device atomic per hit took 11 + 3.5 ms, this form with 64-bit keys in slices
+// of 8192 positions (two per row there) 5.1 + 0.7 ms.  Bound by the latency of
+// the entries and keys: a time frame of 64 collisions took 1390 us with keys
+// loaded behind the entries and written out, 1119 now (8 entries a thread in
+// flight for 4: 1510).
 constexpr int kSelRowBytes = 65536;      // LDS key table of one block
 constexpr int kSelRowBlock = 1024;
 constexpr int kSelRowUnroll = 4;          // tracklet entries loaded together
@@ -100,18 +103,11 @@ struct Key32 {
         const int64_t id = (int64_t)(0xFFFFFFFFull - (k & 0xFFFFFFFFull));
         return (nh << 24) | (0xFFFFFFu - (unsigned)(id - begin));
     }
-    __device__ unsigned long long unpack(T k) const
-    {
-        if (!k) return 0ull;
-        const int64_t id = begin + (int64_t)(0xFFFFFFu - (k & 0xFFFFFFu));
-        return ((unsigned long long)(k >> 24) << 32) | (0xFFFFFFFFull - (unsigned long long)id);
-    }
 };
 struct Key64 {
     using T = unsigned long long;
     int64_t begin;
     __device__ T pack(unsigned long long k) const { return k; }
-    __device__ unsigned long long unpack(T k) const { return k; }
 };
 
 // k-th big sector of [sec_lo, sec_lo + n_sec) (all threads of the block)
@@ -144,8 +140,7 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
     const tpc_sector* __restrict__ sec, int sec_lo, int n_sec, int n_big, int n_rows,
     const int32_t* __restrict__ bin_start, const int32_t* __restrict__ t_hits,
     const int64_t* __restrict__ sec_start, int64_t count_cap, int64_t cap, int64_t n_words,
-    const unsigned long long* __restrict__ tkey, unsigned long long* __restrict__ hitkey,
-    unsigned long long* __restrict__ kbits)
+    const unsigned long long* __restrict__ tkey, unsigned long long* __restrict__ kbits)
 {
     using T = typename KF::T;
     constexpr int kLds = kSelRowBytes / (int)sizeof(T);
@@ -174,6 +169,17 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
     unsigned long long* __restrict__ kb = kbits + (int64_t)r * n_words;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t bd = blockDim.x;
+    // the row's entries and the keys of their tracklets, all in flight (a key
+    // loaded only for a hit waits for the entry first)
+    auto load = [&](int64_t t0, int* h, unsigned long long* tk) {
+#pragma unroll
+        for (int u = 0; u < kSelRowUnroll; ++u) {
+            const int64_t t = t0 + u * bd;
+            const bool in = t >= lo && t < hi;
+            h[u] = in ? row[t] : -1;
+            tk[u] = in ? tkey[t] : 0ull;
+        }
+    };
     for (int ps = p0, slice = 0; ps < p1; ps += kLds, ++slice) {
         const int np = p1 - ps < kLds ? p1 - ps : kLds;
         for (int k = threadIdx.x; k < np; k += blockDim.x) kl[k] = 0;
@@ -181,29 +187,22 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
         // claims: kSelRowUnroll entries per thread in flight
         for (int64_t t0 = a0 + threadIdx.x; t0 < hi; t0 += bd * kSelRowUnroll) {
             int h[kSelRowUnroll];
-#pragma unroll
-            for (int u = 0; u < kSelRowUnroll; ++u) {
-                const int64_t t = t0 + u * bd;
-                h[u] = t >= lo && t < hi ? row[t] : -1;
-            }
+            unsigned long long tk[kSelRowUnroll];
+            load(t0, h, tk);
 #pragma unroll
             for (int u = 0; u < kSelRowUnroll; ++u) {
                 const unsigned o = (unsigned)(h[u] - ps);
                 if (h[u] < 0 || o >= (unsigned)np) continue;
-                const T key = kf.pack(tkey[t0 + u * bd]);
+                const T key = kf.pack(tk[u]);
                 if (key) atomicMax(&kl[o], key);
             }
         }
         __syncthreads();
-        for (int k = threadIdx.x; k < np; k += blockDim.x) hitkey[ps + k] = kf.unpack(kl[k]);
         // kept bits, kSelRowUnroll waves' worth of entries per thread in flight
         for (int64_t t0 = a0 + threadIdx.x; t0 < a1; t0 += bd * kSelRowUnroll) {
             int h[kSelRowUnroll];
-#pragma unroll
-            for (int u = 0; u < kSelRowUnroll; ++u) {
-                const int64_t t = t0 + u * bd;
-                h[u] = t >= lo && t < hi ? row[t] : -1;
-            }
+            unsigned long long tk[kSelRowUnroll];
+            load(t0, h, tk);
 #pragma unroll
             for (int u = 0; u < kSelRowUnroll; ++u) {
                 const int64_t t = t0 + u * bd;
@@ -211,7 +210,7 @@ __global__ __launch_bounds__(kSelRowBlock) void k_sel_rows_big(
                 bool kept = false;
                 const unsigned o = (unsigned)(h[u] - ps);
                 if (h[u] >= 0 && o < (unsigned)np) {
-                    const T key = kf.pack(tkey[t]);
+                    const T key = kf.pack(tk[u]);
                     kept = key && kl[o] == key;
                 }
                 const unsigned long long mask = __ballot(kept);
@@ -268,12 +267,16 @@ __global__ __launch_bounds__(kBlock) void k_sel_count_bits(
 }
 
 // Per tracklet found: 1 << 32 | kept if it becomes a track, else 0, and the
-// sum of every tile.  Tiles past the tracklets found leave at once (over the
+// sum of every tile.  With prefix a track's kept counts turn into the hits
+// before each chunk: with big sectors the writer, adding up the counts before
+// its chunk, read ten bytes more a chunk (64-collision frame: 1440 us, now
+// 1127 and 21 here; a central event would win 2 us and lose 5).  Tiles past the tracklets found leave at once (over the
 // whole capacity, with a pass to clear it, this and the scan took 60 us more
 // on 512 sectors).
 __global__ __launch_bounds__(kBlock) void k_sel_len(
     int n_chunks, tpc_params prm, const tpc_status* __restrict__ status, int64_t count_cap,
-    const uint8_t* __restrict__ ccnt, uint64_t* __restrict__ tlen, int64_t* __restrict__ partials)
+    bool prefix, uint8_t* __restrict__ ccnt, uint64_t* __restrict__ tlen,
+    int64_t* __restrict__ partials)
 {
     __shared__ uint64_t lds[kBlock / kWave];
     const int64_t m = status->n_starts < count_cap ? status->n_starts : count_cap;
@@ -299,6 +302,29 @@ __global__ __launch_bounds__(kBlock) void k_sel_len(
             kept[k] >= prm.min_track_hits ? ((1ull << 32) | (uint64_t)kept[k]) : 0ull;
         tlen[t] = v;
         s += v;
+    }
+    // kBatch chunks of every tracklet in flight
+    constexpr int kBatch = 4;
+    int before[kScanItems] = {};
+    for (int q0 = 0; prefix && q0 < n_chunks; q0 += kBatch) {
+        int c[kBatch][kScanItems];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k) {
+                const int64_t t = b0 + k * kBlock + threadIdx.x;
+                const int q = q0 + j < n_chunks ? q0 + j : n_chunks - 1;
+                c[j][k] = ccnt[q * count_cap + (t < m ? t : m - 1)];
+            }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k) {
+                const int64_t t = b0 + k * kBlock + threadIdx.x;
+                if (q0 + j < n_chunks && t < m && kept[k] >= prm.min_track_hits)
+                    ccnt[(q0 + j) * count_cap + t] = (uint8_t)before[k];
+                before[k] += c[j][k];
+            }
     }
     const uint64_t tot = block_sum(s, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = (int64_t)tot;
@@ -393,14 +419,24 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(
     const int q = blockIdx.y;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < m;
          t += (int64_t)gridDim.x * blockDim.x) {
-        if (!tlen[t]) continue;
+        const uint64_t len = tlen[t];
+        if (!len) continue;
         const uint64_t to = toff[t];
         int64_t o = (int64_t)(to & 0xFFFFFFFFull);
         if (q == 0)
             sel_write_track(t, (int64_t)(to >> 32), o, t_start, sec, gsr, trk_off, trk_tracklet,
                             trk_side, trk_cap);
-        if (!ccnt[q * count_cap + t]) continue;     // the chunk keeps nothing
-        for (int j = 0; j < q; ++j) o += ccnt[j * count_cap + t];
+        // big sectors: hits before the chunk, else hits of each chunk
+        const int c = ccnt[q * count_cap + t];
+        if (kbits) {
+            const int upto = q + 1 < (int)gridDim.y ? (int)ccnt[(q + 1) * count_cap + t]
+                                                    : (int)(len & 0xFFFFFFFFull);
+            if (upto == c) continue;                // the chunk keeps nothing
+            o += c;
+        } else {
+            if (!c) continue;
+            for (int j = 0; j < q; ++j) o += ccnt[j * count_cap + t];
+        }
         if (kbits && tkey[t] != kKeyNotBig) {
             sel_write_bits(t, q * kSelRows, n_rows, o, t_hits, cap, kbits, n_words, out, hit_cap);
             continue;
@@ -511,14 +547,12 @@ int run_select_keys(const tpc_problem* p, int sec_lo, int sec_hi, tpc_grid grid,
             TPC_LAUNCH(k_sel_rows_big<Key32>, gr, dim3(kSelRowBlock), 0, st, p->d_sectors, sec_lo,
                        sec_hi - sec_lo, n_big, p->n_rows, (const int32_t*)grid.bin_start,
                        (const int32_t*)trl.hits, (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
-                       (const unsigned long long*)ws.tkey, (unsigned long long*)ws.hitkey,
-                       (unsigned long long*)ws.kbits);
+                       (const unsigned long long*)ws.tkey, (unsigned long long*)ws.kbits);
         else if (n_big)
             TPC_LAUNCH(k_sel_rows_big<Key64>, gr, dim3(kSelRowBlock), 0, st, p->d_sectors, sec_lo,
                        sec_hi - sec_lo, n_big, p->n_rows, (const int32_t*)grid.bin_start,
                        (const int32_t*)trl.hits, (const int64_t*)ws.sec_start, count_cap, trl.capacity, n_words,
-                       (const unsigned long long*)ws.tkey, (unsigned long long*)ws.hitkey,
-                       (unsigned long long*)ws.kbits);
+                       (const unsigned long long*)ws.tkey, (unsigned long long*)ws.kbits);
         TPC_LAUNCH(k_sel_count_bits, dim3(gx), dim3(kBlock), 0, st, p->n_rows, lo, hi, count_cap,
                    n_words, (const unsigned long long*)ws.tkey,
                    (const unsigned long long*)ws.kbits, ws.ccnt);
@@ -534,7 +568,7 @@ int run_select_compact(const tpc_problem* p, tpc_grid grid, int64_t count_cap,
     const unsigned gx = sel_grid_x(count_cap);
     const int64_t nt = ceil_div(count_cap > 0 ? count_cap : 1, kScanTile);
     TPC_LAUNCH(k_sel_len, dim3((unsigned)nt), dim3(kBlock), 0, st, sel_chunks(p->n_rows),
-               p->params, (const tpc_status*)ws.status, count_cap, (const uint8_t*)ws.ccnt,
+               p->params, (const tpc_status*)ws.status, count_cap, any_sel_big(p), ws.ccnt,
                ws.tlen, ws.partials);
     if (nt <= kScanSelf) {
         TPC_LAUNCH(k_sel_offsets<true>, dim3((unsigned)nt), dim3(kBlock), 0, st,
