@@ -1129,6 +1129,7 @@ void k_refit_adj(
                 if (kStride == 2) prev = next;
             }
             // hits lo .. top, but hit 2: kGrads lanes write one track's run
+            __syncthreads();
             const int i = lo + (lane & (kGrads - 1));
             for (int l = lane / kGrads; l < kWave; l += kWave / kGrads) {
                 const int al = __shfl(a, l, kWave), nl = __shfl(ne, l, kWave);
@@ -1137,6 +1138,7 @@ void k_refit_adj(
                     gz[al + i] = grads[1][l][i - lo];
                 }
             }
+            __syncthreads();              // the next slots go to the same place
             top = lo - 1;
         }
         if (!fit) continue;
