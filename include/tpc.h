@@ -537,7 +537,8 @@ int tpc_refit(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows, const float
               float* checkpoints, size_t ck_bytes, void* stream);
 
 /* Bytes of the checkpoint buffer of tpc_refit / tpc_refit_adjoint for
- * n_tracks tracks (capacity) of at most n_rows hits. */
+ * n_tracks tracks (capacity) of at most n_rows hits.  Never less for more
+ * tracks or rows: a buffer for the largest set serves every smaller one. */
 int tpc_refit_checkpoint_size(int64_t n_tracks, int32_t n_rows, size_t* h_bytes);
 
 /* Bytes of workspace for tpc_refit_adjoint. */

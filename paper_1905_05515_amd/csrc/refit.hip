@@ -20,6 +20,7 @@
 // then 1.55, on 400 tracks, with the short division and root sequences and
 // without waits for hits); many, the checkpoints (80 or 40 bytes a hit
 // written and read back) and then the adjoint's instructions.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -1334,7 +1335,9 @@ constexpr int64_t kSparseTracks = int64_t(1) << 16;
 
 // The checkpoint buffer: the tiles, then the tile order (int32 per track),
 // the per-(key, run) counts of the ordering, its scan partials and the
-// packed hits.
+// packed hits.  The tiles have the room that kSparseTracks - 1 tracks with
+// every state need, also where every second one is kept: a buffer for n
+// tracks serves every smaller set.
 struct CkLayout {
     size_t order_off, cnt_off, part_off, yz_off, row_off, bad_off, total;
     int64_t nblk;
@@ -1358,8 +1361,13 @@ static CkLayout ck_layout(int64_t n_tracks, int n_rows)
     L.nkeys = n_rows + 2;
     const int64_t ncnt = L.nblk * L.nkeys;
     L.stride = ck_stride(n_tracks);
-    L.order_off = ck_align(sizeof(float) * (size_t)tiles * kWave *
-                           (size_t)ck_slots(n_rows, L.stride) * 20);
+    auto states = [&](int64_t n, int stride) {
+        return sizeof(float) * (size_t)ceil_div(n, kWave) * kWave *
+               (size_t)ck_slots(n_rows, stride) * 20;
+    };
+    const size_t sparse = states(n_tracks, L.stride);
+    const size_t dense = states(std::min(n_tracks, kSparseTracks - 1), 1);
+    L.order_off = ck_align(std::max(sparse, dense));
     L.cnt_off = L.order_off + ck_align(sizeof(int32_t) * (size_t)(n_tracks > 0 ? n_tracks : 1));
     L.part_off = L.cnt_off + ck_align(sizeof(int32_t) * (size_t)ncnt);
     L.yz_off = L.part_off + ck_align(sizeof(int64_t) * (size_t)(ceil_div(ncnt, kScanTile) + 1));
