@@ -548,7 +548,9 @@ int tpc_refit_workspace_size(int64_t n_tracks, size_t* h_bytes);
  * dL/dy and dL/dz of every raw hit (grad_y, grad_z [n_hits]) and
  * dL/dtheta (grad_theta[16], a deterministic reduction).  Needs the
  * checkpoints and status of tpc_refit with the same inputs; tracks with
- * status != 0 contribute zero. */
+ * status != 0 contribute zero.  The hits' rows and coordinates are those the
+ * forward pass left in the checkpoints: hits.row, y, z and idx must be given
+ * as for tpc_refit but are not read again (off, side and d_count are). */
 int tpc_refit_adjoint(tpc_context* ctx, tpc_track_hits hits, int32_t n_rows,
                       const float* d_row_x, const tpc_params* h_params,
                       const tpc_calib_model* h_model, const float* d_theta,

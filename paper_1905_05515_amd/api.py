@@ -669,7 +669,9 @@ def refit_adjoint(ctx: Context, hits: TrackHits, row_x: torch.Tensor, prm: dict,
     + sum_k grad_x[k] x_last[k] when either seed is given): (grad_y, grad_z,
     grad_theta), grad_y/grad_z per hit entry of the track list.  `out` (dict
     with ws, gy, gz, gt of an earlier call, or any of them) is reused;
-    entries of tracks past the device track count are not written."""
+    entries of tracks past the device track count are not written.  The hits
+    are the ones `fwd` was made with, kept in its checkpoints: y, z (and the
+    coordinates in `hits`) are taken as in refit but not read again."""
     dev = hits.row.device
     nb = C.c_size_t()
     L.check(L.lib().tpc_refit_workspace_size(hits.n_tracks, C.byref(nb)), "workspace")

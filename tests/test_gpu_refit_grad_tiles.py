@@ -48,3 +48,27 @@ def test_mixed_lengths_in_a_tile(n_tracks):
         assert torch.equal(s1, status[k:k + 1])
         assert torch.equal(y1, gy[off[k]:off[k + 1]]), (k, lens[k])
         assert torch.equal(z1, gz[off[k]:off[k + 1]]), (k, lens[k])
+
+
+@pytest.mark.parametrize("gather", [False, True])
+def test_hits_are_those_of_the_forward_pass(gather):
+    """The adjoint takes rows and coordinates from the checkpoints: the same
+    gradients when the caller's arrays hold something else by then."""
+    rs = synth.make_config5(n_tracks=200)
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
+    prm = synth.default_params()
+    rx, th = t(rs.row_x), t(rs.theta_eval)
+    idx = torch.arange(rs.n_hits, dtype=torch.int32, device="cuda") if gather else None
+    h = api.TrackHits(off=t(rs.trk_off), row=t(rs.row), y=t(rs.y), z=t(rs.z), idx=idx)
+    out = api.refit(ctx(), h, rx, prm, th)
+    g = torch.ones(rs.n_tracks, device="cuda")
+    want = [v.clone() for v in api.refit_adjoint(ctx(), h, rx, prm, th, out, g)]
+    other = torch.zeros_like(h.y)
+    got = api.refit_adjoint(ctx(), h, rx, prm, th, out, g, y=other, z=other)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    for v in (h.row, h.y, h.z):
+        v.zero_()
+    got = api.refit_adjoint(ctx(), h, rx, prm, th, out, g)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
