@@ -204,8 +204,8 @@ int tpc_context_destroy(tpc_context* ctx);
 
 /* Launch shapes of a context (none changes any output; every field 0 is
  * the library's own choice).  tracklet_form: one of
- * the values below; all of them select the one form there is (the hit lists
- * written row by row as the waves walk the rows).  neighbour_block: threads
+ * the values below, accepted and without effect: there is one form (the hit
+ * lists written row by row as the waves walk the rows).  neighbour_block: threads
  * per block of the neighbour kernel (64, 128 or 256).  persistent_scale: tile size
  * multiplier of the persistent form (1, 2, 4 or 8; automatic grows it with
  * the clusters per resident block).  persistent_blocks_per_cu: blocks of

@@ -201,11 +201,11 @@ def set_tuning(ctx: "Context", **kw):
 
 
 # launch shapes the shape tuner tries, per tracking form, one field at a time
+# (tracklet_form is accepted, but there is one form: nothing to time)
 TUNE_SHAPES = {
-    "staged": (("tracklet_form", (0, 1, 2, 3)), ("neighbour_block", (256, 128, 64))),
-    "per_sector": (("tracklet_form", (0, 1, 2, 3)), ("neighbour_block", (256, 128, 64))),
-    "persistent": (("persistent_scale", (0, 1, 2, 4, 8)), ("persistent_blocks_per_cu", (0, 2, 1)),
-                   ("tracklet_form", (0,))),
+    "staged": (("neighbour_block", (256, 128, 64)),),
+    "per_sector": (("neighbour_block", (256, 128, 64)),),
+    "persistent": (("persistent_scale", (0, 1, 2, 4, 8)), ("persistent_blocks_per_cu", (0, 2, 1))),
 }
 
 

@@ -165,8 +165,7 @@ int tpc_track_batch(tpc_context* ctx, const tpc_problem* h_prob, tpc_clusters in
     for (const void* q : ptrs) key = mix(key, (uint64_t)(uintptr_t)q);
     key = mix(key, (uint64_t)starts.capacity);
     if (tune)
-        key = mix(key, (uint64_t)(uint32_t)tune->tracklet_form |
-                           (uint64_t)(uint32_t)tune->neighbour_block << 8 |
+        key = mix(key, (uint64_t)(uint32_t)tune->neighbour_block << 8 |
                            (uint64_t)(uint32_t)tune->persistent_scale << 24 |
                            (uint64_t)(uint32_t)tune->persistent_blocks_per_cu << 32);
     key = mix(key, (uint64_t)tracklets.capacity);
