@@ -162,12 +162,13 @@ struct TimerScope {
     ~TimerScope() { set_current_timer(saved); }
 };
 
-#define TPC_LAUNCH(k, g, b, sh, st, ...)                      \
+#define TPC_LAUNCH_AS(name, k, g, b, sh, st, ...)             \
     do {                                                      \
-        ::tpc::timer_begin(#k, st);                           \
+        ::tpc::timer_begin(name, st);                         \
         hipLaunchKernelGGL(k, g, b, sh, st, __VA_ARGS__);     \
         ::tpc::timer_end(st);                                 \
     } while (0)
+#define TPC_LAUNCH(k, ...) TPC_LAUNCH_AS(#k, k, __VA_ARGS__)
 
 // ---- launch helpers (host) --------------------------------------------------
 

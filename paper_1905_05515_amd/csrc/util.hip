@@ -112,14 +112,16 @@ void launch_scan(const T* in, T* out, int64_t n, bool write_total, int64_t* tota
     if (nt > 1)
         TPC_LAUNCH(k_scan_tile_sums<T>, dim3((unsigned)nt), dim3(kBlock), 0, st, in, n, partials);
     if (nt <= kScanSelf) {
-        TPC_LAUNCH((k_scan_tiles<T, true>), dim3((unsigned)nt), dim3(kBlock), 0, st, in, out, n,
-                   (const int64_t*)partials, carry0, total_dst, write_total ? 1 : 0);
+        TPC_LAUNCH_AS("k_scan_tiles<T, true>", (k_scan_tiles<T, true>), dim3((unsigned)nt),
+                      dim3(kBlock), 0, st, in, out, n, (const int64_t*)partials, carry0,
+                      total_dst, write_total ? 1 : 0);
         return;
     }
     TPC_LAUNCH(k_scan_partials, dim3(1), dim3(kBlock), 0, st, partials, nt, (const int64_t*)nullptr,
                carry0, total_dst);
-    TPC_LAUNCH((k_scan_tiles<T, false>), dim3((unsigned)nt), dim3(kBlock), 0, st, in, out, n,
-               (const int64_t*)partials, carry0, total_dst, write_total ? 1 : 0);
+    TPC_LAUNCH_AS("k_scan_tiles<T, false>", (k_scan_tiles<T, false>), dim3((unsigned)nt),
+                  dim3(kBlock), 0, st, in, out, n, (const int64_t*)partials, carry0, total_dst,
+                  write_total ? 1 : 0);
 }
 void launch_scan_partials(int64_t* partials, int64_t nt, const int64_t* carry_in,
                           int64_t* total_dst, hipStream_t st)
@@ -246,7 +248,6 @@ void timer_begin(const char* name, hipStream_t st)
 {
     KernelTimer* t = t_timer;
     if (!t || capturing(st)) return;
-    if (*name == '(') ++name;
     for (const char* c = name; *c && *c != '<'; ++c)      // drop namespace qualifiers
         if (c[0] == ':' && c[1] == ':') name = c + 2;
     hipEvent_t e = t->take();
