@@ -633,8 +633,9 @@ int tpc_timing_report(tpc_context* ctx, int max_kernels, const char** h_names,
                       int64_t* h_launches, double* h_total_ms, int* h_count);
 
 /* Self-check of the short binary32 sequences the kernels use for 1 / b (op
- * 0: over their range, 2: for any b), sqrt(b) (op 1) and a / b (op 3, eight
- * numerators per denominator) against the correctly rounded operators, with
+ * 0: over their range, 2: for any b), sqrt(b) (op 1) and a / b (op 3, 16
+ * numerators per denominator, 4: also zeros, infinities and NaN as
+ * numerators) against the correctly rounded operators, with
  * every bit pattern in [lo, hi) as operand b; the number of results that
  * differ is added to *d_mismatches (device memory). */
 int tpc_check_exact_fp32(int op, uint32_t lo, uint32_t hi, uint64_t* d_mismatches, void* stream);

@@ -50,14 +50,24 @@ __device__ __forceinline__ float sqrt_exact(float u)
 }
 
 // a / b given r = rcp_exact(b) (not an approximation an ulp off: for a b of
-// all ones, 1 - 2^-24 say, the last step rounds right only with it); 2^-20 <= b <= 2^20 and a zero or
-// 2^-80 <= |a| <= 2^80 (a smaller |a| gives a quotient below 2^-60 that may
-// be off; the quotient of a negative zero is a positive zero)
+// all ones, 1 - 2^-24 say, the last step rounds right only with it);
+// kDivMin <= |b| <= kDivMax and a zero or 2^-80 <= |a| <= 2^80 (a smaller |a|
+// gives a quotient below 2^-60 that may be off; the quotient of a negative
+// zero is a positive zero)
+constexpr float kDivMin = 0x1p-20f, kDivMax = 0x1p20f;
+
 __device__ __forceinline__ float div_exact(float a, float b, float r)
 {
     float q = a * r;
     q = fmaf(fmaf(-b, q, a), r, q);       // within an ulp
     return fmaf(fmaf(-b, q, a), r, q);
+}
+
+// the same, and the operator's result for zeros of either sign, infinities
+// and NaN in a
+__device__ __forceinline__ float div_exact_special(float a, float b, float r)
+{
+    return __builtin_amdgcn_div_fixupf(div_exact(a, b, r), b, a);
 }
 
 }  // namespace tpc

@@ -51,12 +51,22 @@ struct CalHit {
     float d, u, v;      // calibrated drift, basis coordinates
 };
 
-// iv: the reciprocal of the row's xr tan_half.  (The forward functions write
+// Quotient by a row's xr tan_half; iv: its reciprocal.  kIn: those of all
+// rows are in the short division's range (a geometry of centimetres lies
+// within 2^3 and 2^6).  The kernels branch on it once: with a branch at every
+// hit the refit of 16,783 tracks took 135 us for 128.
+template <bool kIn>
+__device__ __forceinline__ float row_div(float a, float b, float iv)
+{
+    return kIn ? div_exact_special(a, b, iv) : a / b;
+}
+
+// iv, kIn: as for row_div.  (The forward functions write
 // their fused multiply-adds out: left to the compiler, the choice of the
 // product that is fused changed with the code around, and a low-momentum
 // track's gradient with it.  kEnd: a hit that starts a pass or ends the
 // reverse sweep, whose drift is rounded once less, as it always was.)
-template <bool kEnd>
+template <bool kEnd, bool kIn>
 __device__ __forceinline__ CalHit calibrate(const float* th, float xr, float iv, float yr, float zr,
                                             float sd, const CalibModel& cm)
 {
@@ -70,7 +80,7 @@ __device__ __forceinline__ CalHit calibrate(const float* th, float xr, float iv,
     h.d = scale * drift;
     h.z = sd * (kEnd ? fmaf(-scale, drift, cm.DL) : cm.DL - h.d);
     h.u = (xr - cm.UC) * cm.iUS;
-    h.v = div_exact(yr, xr * cm.TH, iv);
+    h.v = row_div<kIn>(yr, xr * cm.TH, iv);
     const float w = h.d * cm.iDL;
     const float b[7] = {1.0f, h.u, h.v, h.u * h.u, h.u * h.v, h.v * h.v, w};
     float dr = th[2], drphi = th[9];
@@ -86,6 +96,7 @@ __device__ __forceinline__ CalHit calibrate(const float* th, float xr, float iv,
 
 // reverse of calibrate: adjoints (X, Y, Z) of the calibrated point ->
 // raw (y, z) adjoints, accumulated theta adjoint
+template <bool kIn>
 __device__ __forceinline__ void calibrate_adj(const float* th, const CalHit& h, float sd,
                                               const CalibModel& cm, float X, float Y, float Z,
                                               double* gth, float& gyr, float& gzr)
@@ -107,21 +118,27 @@ __device__ __forceinline__ void calibrate_adj(const float* th, const CalHit& h, 
         bb[j] = X * th[2 + j] + Y * th[9 + j];
     }
     const float vb = bb[2] + bb[4] * h.u + 2.0f * bb[5] * h.v;
-    gyr = Y + div_exact(vb, h.xr * cm.TH, h.iv);
+    gyr = Y + row_div<kIn>(vb, h.xr * cm.TH, h.iv);
     const float db = bb[6] * cm.iDL - Z * sd;
     gth[0] += (double)(db * (h.dr - cm.VD * th[1]));
     gth[1] += (double)(-db * (1.0f + th[0]) * cm.VD);
     gzr = -sd * (1.0f + th[0]) * db;
 }
 
-// Per pad row: the plane and the reciprocal of plane times tan_half, in LDS.
-__device__ __forceinline__ void load_rows(const float* __restrict__ row_x, int n_rows, float th,
+// Per pad row: the plane and the reciprocal of plane times tan_half, in LDS;
+// true if all of these are in the short division's range (a barrier: the
+// table is whole when it returns).
+__device__ __forceinline__ bool load_rows(const float* __restrict__ row_x, int n_rows, float th,
                                           float2* xs)
 {
+    bool in = true;
     for (int i = threadIdx.x; i < 256; i += blockDim.x) {
         const float x = i < n_rows ? row_x[i] : 0.0f;
+        const float b = fabsf(x * th);
+        in &= i >= n_rows || (b >= kDivMin && b <= kDivMax);
         xs[i] = make_float2(x, 1.0f / (x * th));
     }
+    return __builtin_amdgcn_readfirstlane(__syncthreads_and(in));
 }
 
 struct Prop {
@@ -154,6 +171,7 @@ __device__ __forceinline__ bool prop_fwd(float* p, float* C, float dx, float cur
         P.T = (s + P.s2) * P.icc;
         P.q = sqrt_exact(fmaf(P.T, P.T, 1.0f));
         P.iq = rcp_exact(P.q);
+        P.LT = div_exact(dx * P.T, P.q, P.iq);   // 1 <= q <= 2^12
     } else {
         const float c1 = sqrtf(u1), c2 = sqrtf(u2);
         P.icc = 1.0f / (c1 + c2);
@@ -164,6 +182,7 @@ __device__ __forceinline__ bool prop_fwd(float* p, float* C, float dx, float cur
         P.T = (s + P.s2) * P.icc;
         P.q = sqrtf(fmaf(P.T, P.T, 1.0f));
         P.iq = 1.0f / P.q;
+        P.LT = dx * P.T / P.q;
     }
     P.L = dx * P.q;
     P.a = 0.5f * P.k * P.L;
@@ -173,7 +192,6 @@ __device__ __forceinline__ bool prop_fwd(float* p, float* C, float dx, float cur
     P.Ts = fmaf(P.T, P.e1 + P.e2, 2.0f) * P.icc;
     P.kdx = curv * dx;
     P.Tw = P.kdx * fmaf(P.T, P.e2, 1.0f) * P.icc;
-    P.LT = div_exact(dx * P.T, P.q, P.iq);
     P.G1 = fmaf(P.a2, fmaf(P.a2, fmaf(P.a2, 5.0f / 16.0f, 3.0f / 8.0f), 0.5f), 1.0f);
     P.Sk = P.L * P.L * P.a * fmaf(P.a2, fmaf(P.a2, 15.0f / 112.0f, 3.0f / 20.0f), 1.0f / 6.0f);
     P.ys = dx * P.Ts;
@@ -864,21 +882,15 @@ constexpr std::false_type kNo{};
 // where the forward pass reads its hits
 enum { kCsr = 0, kCsrIndex = 1, kPacked = 2 };
 
-template <int kFrom>
-__global__ __launch_bounds__(kWave) void k_refit_fwd(
-    HitRows in, PackedHits packed, const int8_t* __restrict__ side, const int64_t* __restrict__ d_count,
-    int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
-    const float* __restrict__ d_theta, float* __restrict__ par, float* __restrict__ cov,
-    float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck, int stride,
-    const int32_t* __restrict__ order)
+template <int kFrom, bool kIn>
+__device__ __forceinline__ void refit_fwd(
+    const float* th, const float2* xs, float4* hits, const HitRows& in, const PackedHits& packed,
+    const int8_t* __restrict__ side, const int64_t* __restrict__ d_count, int64_t n_tracks,
+    int n_rows, const tpc_params& prm, const CalibModel& cm, float* __restrict__ par,
+    float* __restrict__ cov, float* __restrict__ chi2_out, int32_t* __restrict__ status,
+    float* __restrict__ ck, int stride, const int32_t* __restrict__ order)
 {
-    __shared__ float th[16];
-    __shared__ float2 xs[256];
-    __shared__ float4 hits[kFrom == kPacked ? kWave : kChunk * kWave];
     constexpr bool kIdx = kFrom == kCsrIndex;
-    load_theta(d_theta, th);
-    load_rows(row_x, n_rows, cm.TH, xs);
-    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     float4* col = hits + lane;
     const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
@@ -941,7 +953,7 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
             const PackedCol hp = packed_col(packed, tb + lane, n_rows);
             auto cal = [&](const RawHit& r, auto end) {
                 const float2 x = xs[r.row];
-                return calibrate<end()>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
+                return calibrate<end(), kIn>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
             };
             // hits of the next two slots, in flight
             RawHit r1{}, r2{};
@@ -977,7 +989,7 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
                 }
                 auto cal = [&](int k, auto end) {
                     const float4 r = col[k * kWave];
-                    return calibrate<end()>(th, r.x, r.w, r.y, r.z, sd, cm);
+                    return calibrate<end(), kIn>(th, r.x, r.w, r.y, r.z, sd, cm);
                 };
                 if (i0 == 0 && alive) start(cal(0, kYes), cal(2, kYes));
                 const int i_hi = i0 + kChunk < M ? i0 + kChunk : M;
@@ -1006,28 +1018,41 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
     }
 }
 
-// Hit gradients of kGrads slots leave together: 16 lanes write 16 entries of
-// one track, so that most of a line is written by one instruction.
-constexpr int kGrads = 16;
-
-template <int kStride>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
-void k_refit_adj(
-    const int32_t* __restrict__ off, PackedHits packed, const int8_t* __restrict__ side,
-    const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
-    const float* __restrict__ d_theta, const float* __restrict__ ck,
-    const int32_t* __restrict__ status, const float* __restrict__ gchi2,
-    const float* __restrict__ seed_p, const float* __restrict__ seed_x,
-    float* __restrict__ gy, float* __restrict__ gz, double* __restrict__ partials,
+template <int kFrom>
+__global__ __launch_bounds__(kWave) void k_refit_fwd(
+    HitRows in, PackedHits packed, const int8_t* __restrict__ side, const int64_t* __restrict__ d_count,
+    int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
+    const float* __restrict__ d_theta, float* __restrict__ par, float* __restrict__ cov,
+    float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck, int stride,
     const int32_t* __restrict__ order)
 {
     __shared__ float th[16];
     __shared__ float2 xs[256];
-    // the hit gradients of kGrads slots, y then z, by lane
-    __shared__ float grads[2][kWave][kGrads + 1];
+    __shared__ float4 hits[kFrom == kPacked ? kWave : kChunk * kWave];
     load_theta(d_theta, th);
-    load_rows(row_x, n_rows, cm.TH, xs);
-    __syncthreads();
+    if (load_rows(row_x, n_rows, cm.TH, xs))
+        refit_fwd<kFrom, true>(th, xs, hits, in, packed, side, d_count, n_tracks, n_rows, prm, cm,
+                               par, cov, chi2_out, status, ck, stride, order);
+    else
+        refit_fwd<kFrom, false>(th, xs, hits, in, packed, side, d_count, n_tracks, n_rows, prm, cm,
+                                par, cov, chi2_out, status, ck, stride, order);
+}
+
+// Hit gradients of kGrads slots leave together: 16 lanes write 16 entries of
+// one track, so that most of a line is written by one instruction.
+constexpr int kGrads = 16;
+
+// grads: the hit gradients of kGrads slots, y then z, by lane
+template <int kStride, bool kIn>
+__device__ __forceinline__ void refit_adj(
+    const float* th, const float2* xs, float (*grads)[kWave][kGrads + 1],
+    const int32_t* __restrict__ off, const PackedHits& packed, const int8_t* __restrict__ side,
+    const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows, const tpc_params& prm,
+    const CalibModel& cm, const float* __restrict__ ck, const int32_t* __restrict__ status,
+    const float* __restrict__ gchi2, const float* __restrict__ seed_p,
+    const float* __restrict__ seed_x, float* __restrict__ gy, float* __restrict__ gz,
+    double* __restrict__ partials, const int32_t* __restrict__ order)
+{
     double gth[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) gth[k] = 0.0;
@@ -1066,7 +1091,7 @@ void k_refit_adj(
         for (int i = 0; i < 15; ++i) G[i] = 0.0f;
         auto cal = [&](const RawHit& r, auto end) {
             const float2 x = xs[r.row];
-            return calibrate<end()>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
+            return calibrate<end(), kIn>(th, x.x, x.y, r.yz.x, r.yz.y, sd, cm);
         };
         CalHit cur{};
         // step i needs hit i - 1, with every second checkpoint hit i - 2 too;
@@ -1121,7 +1146,7 @@ void k_refit_adj(
                     Z2 = mzb;
                 } else {
                     float gyr, gzr;
-                    calibrate_adj(th, cur, sd, cm, Xi, myb, mzb, gth, gyr, gzr);
+                    calibrate_adj<kIn>(th, cur, sd, cm, Xi, myb, mzb, gth, gyr, gzr);
                     grads[0][lane][i - lo] = gyr;
                     grads[1][lane][i - lo] = gzr;
                 }
@@ -1165,10 +1190,10 @@ void k_refit_adj(
         X2 += dXb;
         X0 -= dXb;
         float gyr, gzr;
-        calibrate_adj(th, h0, sd, cm, X0, Y0, Z0, gth, gyr, gzr);
+        calibrate_adj<kIn>(th, h0, sd, cm, X0, Y0, Z0, gth, gyr, gzr);
         gy[a] = gyr;
         gz[a] = gzr;
-        calibrate_adj(th, h2, sd, cm, X2, Y2, Z2, gth, gyr, gzr);
+        calibrate_adj<kIn>(th, h2, sd, cm, X2, Y2, Z2, gth, gyr, gzr);
         gy[a + 2] = gyr;
         gz[a + 2] = gzr;
     }
@@ -1180,6 +1205,29 @@ void k_refit_adj(
         for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
         if (lane == k) partials[blockIdx.x * 16 + k] = v;
     }
+}
+
+template <int kStride>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2)))
+void k_refit_adj(
+    const int32_t* __restrict__ off, PackedHits packed, const int8_t* __restrict__ side,
+    const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows, const float* __restrict__ row_x, tpc_params prm, CalibModel cm,
+    const float* __restrict__ d_theta, const float* __restrict__ ck,
+    const int32_t* __restrict__ status, const float* __restrict__ gchi2,
+    const float* __restrict__ seed_p, const float* __restrict__ seed_x,
+    float* __restrict__ gy, float* __restrict__ gz, double* __restrict__ partials,
+    const int32_t* __restrict__ order)
+{
+    __shared__ float th[16];
+    __shared__ float2 xs[256];
+    __shared__ float grads[2][kWave][kGrads + 1];
+    load_theta(d_theta, th);
+    if (load_rows(row_x, n_rows, cm.TH, xs))
+        refit_adj<kStride, true>(th, xs, grads, off, packed, side, d_count, n_tracks, n_rows, prm,
+                                 cm, ck, status, gchi2, seed_p, seed_x, gy, gz, partials, order);
+    else
+        refit_adj<kStride, false>(th, xs, grads, off, packed, side, d_count, n_tracks, n_rows, prm,
+                                  cm, ck, status, gchi2, seed_p, seed_x, gy, gz, partials, order);
 }
 
 // sum of the partials of the blocks that had tracks, in a fixed order: block
@@ -1254,7 +1302,7 @@ __global__ __launch_bounds__(kBlock) void k_vertex_residual(
             const int c = idx ? idx[a + n - 1] : a + n - 1;
             const float sd = side ? (float)side[t] : 1.0f;
             const float xr = row_x[row[c]];
-            const float xl = calibrate<true>(th, xr, 1.0f / (xr * cm.TH), y[c], z[c], sd, cm).x;
+            const float xl = calibrate<true, false>(th, xr, 0.0f, y[c], z[c], sd, cm).x;
             float p[5], C[15];
 #pragma unroll
             for (int i = 0; i < 5; ++i) p[i] = par[t * 5 + i];
