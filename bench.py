@@ -344,7 +344,7 @@ def main():
         log(f"[bench]   {k:28s} {v['avg_ms'] * 1e3:9.1f} us x {v['launches'] // args.steps}")
     n_cl = ev.n_clusters
     n_hits_trk = int(st["n_track_hits"])
-    roof = roofline(dom, kernels[dom]["avg_ms"], st, n_cl, n_hits_trk)
+    roof = roofline(dom, kernels[dom]["avg_ms"], st, n_cl, n_hits_trk, e.track_capacity)
     roof["traffic"] = counter_traffic(dom.split("<")[0], "batched_set")
     roof["source_sha256"] = source_hash(dom.split("<")[0])
 
@@ -606,7 +606,7 @@ def central_bench(args, api, synth, prm, dev, tuned_batch, streams=()):
 
     n_cl = ev.n_clusters
     n_hits_trk = int(st["n_track_hits"])
-    roof = roofline(dom, kernels[dom]["avg_ms"], st, n_cl, n_hits_trk)
+    roof = roofline(dom, kernels[dom]["avg_ms"], st, n_cl, n_hits_trk, e.track_capacity)
     roof["traffic"] = counter_traffic(dom.split("<")[0], "central_event")
     roof["source_sha256"] = source_hash(dom.split("<")[0])
     res = {"workload": "central Pb-Pb-like event: 36 sectors, 8000 primaries + 10% secondaries "
@@ -666,7 +666,21 @@ def compress_bench(args, api, ctx, e, ev, stream):
     return res
 
 
-def roofline(name, avg_ms, st, n_cl, n_trk_hits):
+# track capacity from which the refit keeps every second state only
+REFIT_SPARSE_TRACKS = 1 << 16
+
+
+def refit_bytes_per_hit(kernel, track_capacity):
+    """Bytes a track hit costs a refit kernel at least: the hit (row, y, z;
+    read and written to be packed), 80 B of checkpoint per state kept, two
+    gradients out of the adjoint."""
+    if kernel == "k_refit_pack":
+        return 9 + 9
+    state = 40 if track_capacity >= REFIT_SPARSE_TRACKS else 80
+    return 9 + state + (8 if kernel == "k_refit_adj" else 0)
+
+
+def roofline(name, avg_ms, st, n_cl, n_trk_hits, track_capacity):
     """Algorithmic traffic (bytes) or operations per launch of a kernel."""
     sec = avg_ms * 1e-3
     base = name.split("<")[0]
@@ -702,9 +716,8 @@ def roofline(name, avg_ms, st, n_cl, n_trk_hits):
                 "frac_of_issue_ceiling": tf / ALU_ISSUE_PEAK_TOPS,
                 "flops_per_launch": fl, "propagations": st["n_propagations"],
                 "updates": st["n_updates"], "candidates": st["n_candidates"]}
-    if base in ("k_refit_fwd", "k_refit_adj"):
-        # packed hit, every second state a checkpoint (two gradients)
-        per_hit = 9 + (40 if base == "k_refit_fwd" else 48)
+    if base in ("k_refit_pack", "k_refit_fwd", "k_refit_adj"):
+        per_hit = refit_bytes_per_hit(base, track_capacity)
         b = per_hit * n_trk_hits
         gbs = b / sec / 1e9
         return {"kernel": name, "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
@@ -1131,9 +1144,8 @@ def refit_bench(args, api, synth, ctx, stream, prm, dev):
     fwd_ms, adj_ms = (sum(ms_ for k, (_, ms_) in kt.items() if k.split("<")[0] == base) /
                       sum(n for k, (n, _) in kt.items() if k.split("<")[0] == base)
                       for base in ("k_refit_fwd", "k_refit_adj"))
-    # a million tracks: every second state is a checkpoint
-    fwd_b = nh * (9 + 40)
-    adj_b = nh * (9 + 40 + 8)
+    fwd_hit, adj_hit = (refit_bytes_per_hit(k, rs.n_tracks) for k in ("k_refit_fwd", "k_refit_adj"))
+    fwd_b, adj_b = nh * fwd_hit, nh * adj_hit
     log(f"[bench] refit+adjoint {ms:.3f} ms per pass, {rs.n_tracks / (ms * 1e-3):.3e} tracks/s")
     calib = calibration_bench(api, ctx, stream, prm, rs, h, rx, th, steps)
     return {
@@ -1147,11 +1159,11 @@ def refit_bench(args, api, synth, ctx, stream, prm, dev):
         "roofline_fwd": {"bound": "hbm", "achieved": fwd_b / (fwd_ms * 1e-3) / 1e9,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": fwd_b / (fwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                         "algorithmic_bytes_per_hit": 49},
+                         "algorithmic_bytes_per_hit": fwd_hit},
         "roofline_adj": {"bound": "hbm", "achieved": adj_b / (adj_ms * 1e-3) / 1e9,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": adj_b / (adj_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                         "algorithmic_bytes_per_hit": 57},
+                         "algorithmic_bytes_per_hit": adj_hit},
     }
 
 
