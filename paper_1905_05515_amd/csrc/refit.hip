@@ -790,11 +790,17 @@ __device__ __forceinline__ int64_t track_at(const int32_t* __restrict__ order, i
 
 // The hits of 64 tracks (consecutive in the tile order) into their tile, one
 // block per (tile, kPackSlots slots; the last block of a tile also looks at
-// the hits past the rows): a wave reads kPackRuns tracks' runs at a time,
-// 64 entries of each, into LDS, and the block writes the tile slot by slot.
+// the hits past the rows), or per tile where there are enough of them to fill
+// the chip: a wave reads kPackRuns tracks' runs at a time, 64 entries of each,
+// into LDS, and the block writes the tile slot by slot.
 // Streaming: 1M tracks' hits, 0.86 GB read and written.
 constexpr int kPackSlots = kWave;
 constexpr int kPackRuns = 8;
+// tiles from which one block takes a tile: four blocks to a compute unit.
+// Blocks of 64 slots find nothing past the longest track of theirs: 300,000
+// tracks of 10 hits 66 us and now 53, of 40 hits 97 and 79, a million of 40 to
+// 152 600 and 562; 66,000 of 10 hits 21 and 20, 400 tracks need the blocks.
+constexpr int64_t kPackWhole = 1024;
 
 __host__ __device__ inline int pack_parts(int n_rows)
 {
@@ -812,10 +818,11 @@ __global__ __launch_bounds__(kBlock) void k_refit_pack(
     constexpr int kWaves = kBlock / kWave;
     const int64_t nt = d_count && *d_count < n_tracks ? *d_count : n_tracks;
     const int parts = pack_parts(n_rows);
-    const int64_t units = (nt + kWave - 1) / kWave * parts;
-    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const int64_t tb = u / parts * kWave;
-        const int part = (int)(u % parts);
+    const int64_t tiles = (nt + kWave - 1) / kWave;
+    const int split = tiles < kPackWhole ? parts : 1;     // blocks per tile
+    for (int64_t u = blockIdx.x; u < tiles * split; u += gridDim.x) {
+        const int64_t tile = u / split, tb = tile * kWave;
+        const int part = (int)(u % split);
         if (threadIdx.x < kWave) {
             const int64_t t = track_at(order, tb + lane, nt);
             int a = 0, n = 0;
@@ -832,7 +839,7 @@ __global__ __launch_bounds__(kBlock) void k_refit_pack(
         }
         __syncthreads();
         const int first = part * kPackSlots;
-        const int past = part + 1 < parts ? first + kPackSlots : longest;
+        const int past = part + 1 < split ? first + kPackSlots : longest;
         for (int i0 = first; i0 < longest && i0 < past; i0 += kPackSlots) {
             const int i = i0 + lane;
             for (int l0 = wid; l0 < kWave; l0 += kWaves * kPackRuns) {
@@ -865,13 +872,17 @@ __global__ __launch_bounds__(kBlock) void k_refit_pack(
             const int n = n_[lane];
             for (int k = wid; k < kPackSlots && i0 + k < n_rows && i0 + k < longest; k += kWaves)
                 if (i0 + k < n) {
-                    const int64_t o = (u / parts * n_rows + i0 + k) * kWave + lane;
+                    const int64_t o = (tile * n_rows + i0 + k) * kWave + lane;
                     out.yz[o] = yz[k][lane];
                     out.row[o] = rw[k][lane];
                 }
             __syncthreads();
         }
-        if (threadIdx.x < kWave) out.bad[(u / parts * parts + part) * kWave + lane] = (uint8_t)bad[lane];
+        if (threadIdx.x < kWave) {
+            uint8_t* b = out.bad + (tile * parts + part) * kWave + lane;
+            *b = (uint8_t)bad[lane];
+            for (int k = 1; k < parts && split == 1; ++k) b[k * kWave] = 0;
+        }
         __syncthreads();
     }
 }
