@@ -525,19 +525,33 @@ __device__ __forceinline__ void load_theta(const float* __restrict__ d_theta, fl
     __syncthreads();
 }
 
-// ---- the hits of a lane's track, without checkpoints ----------------------
-// A lane reads its track's hits kChunk at a time, as vector loads (its run
-// of the CSR is contiguous, at any alignment of 4 bytes), a chunk ahead of
-// their use, and puts them into its own column of LDS when their chunk
-// begins.  The chunk at slot i0 of a track of n hits holds the hits [base,
-// base + kChunk), base = min(i0, n - kChunk), so that the last one reads no
-// entry past the track.  (Loading them cooperatively, as runs of 8 hits of
-// 8 tracks per instruction, and waiting for each instruction's hits took 9000
-// cycles per 8 hits, half of the forward kernel's time on 400 tracks.)
-constexpr int kChunk = 4;
+// ---- the hits of a wave's tracks, without checkpoints ----------------------
+// Read kChunk of every track at a time, a chunk ahead of their use, and put
+// into LDS, a column a track, when their chunk begins.
+//
+// In the order of the track list, a lane reads its own track: its run is
+// contiguous, at any alignment of 4 bytes, so these are vector loads.  The
+// chunk at slot i0 of a track of n hits holds the hits [base, base + kChunk),
+// base = min(i0, n - kChunk), so that the last one reads no entry past the
+// track.  Bound by the chain of a track's steps for few tracks, by the lines
+// of the list for many, which the tracks in flight push out of the L2s between
+// two visits: eight hits a visit, and not four, took 300,000 tracks of 40 to
+// 152 hits from 485 to 360 us and a million from 1330 to 950 (16,783: 127 and
+// 120).
+//
+// Through an index, eight lanes read eight hits of one track and the same of
+// eight more, the index a chunk further ahead (two loads in a row, each
+// waiting for the last, would stand in every chunk's way): bound by a line per
+// hit and array for many tracks, where a lane reading its own track's indices
+// visits more of their lines.  40 to 152 hits at random places (us; a lane its
+// own track, four hits at a time; now): 400 tracks 131, 130; 16,783 179, 162;
+// 66,000 392, 375; 131,072 752, 722; 300,000 1780, 1705.
+// (Waiting for each instruction's hits of eight tracks took 9000 cycles per 8
+// hits, half of the forward kernel's time on 400 tracks.)
+constexpr int kChunk = 8;
+constexpr int kQuads = kChunk / 4;
 
 typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
-typedef int32_t int4_u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t uint32_u __attribute__((aligned(1)));
 
 struct HitRows {
@@ -549,54 +563,38 @@ struct HitRows {
 };
 
 struct HitChunk {
-    float4_u y, z;
-    uint32_t row;      // a byte per hit
+    float4_u y[kQuads], z[kQuads];
+    uint32_t row[kQuads];      // a byte per hit
     int base;
-    int4_u c;          // with an index: clusters of the chunk to load next
 };
 
-// first hit of the chunk at slot i0 of a track of n hits
-__device__ __forceinline__ int chunk_base(int i0, int n)
-{
-    const int b = i0 < n - kChunk ? i0 : n - kChunk;
-    return b > 0 ? b : 0;
-}
-
-// the cluster indices of the chunk at slot i0 of the track at entry a (n
-// hits; three hits: the third stands for a fourth)
-__device__ __forceinline__ void load_index(HitChunk& h, const HitRows& in, int a, int n, int i0)
-{
-    if (n >= kChunk) {
-        h.c = *reinterpret_cast<const int4_u*>(in.idx + a + chunk_base(i0, n));
-    } else {
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) h.c[k] = in.idx[a + (k < n ? k : n - 1)];
-    }
-}
-
-// load the chunk at slot i0; with an index (kIdx) its clusters, whose
-// indices load_index has loaded a chunk earlier (two loads in a row, each
-// waiting for the last, would stand in every chunk's way)
-template <bool kIdx>
+// load the chunk at slot i0 of the track of n hits at entry a (past a short
+// track the last hit again)
 __device__ __forceinline__ void load_chunk(HitChunk& h, const HitRows& in, int a, int n, int i0)
 {
-    h.base = chunk_base(i0, n);
-    const int e = a + h.base;
-    if (!kIdx && n >= kChunk) {
-        h.y = *reinterpret_cast<const float4_u*>(in.y + e);
-        h.z = *reinterpret_cast<const float4_u*>(in.z + e);
-        h.row = *reinterpret_cast<const uint32_u*>(in.row + e);
+    if (n >= kChunk) {
+        h.base = i0 < n - kChunk ? i0 : n - kChunk;
+        const int e = a + h.base;
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) {
+            h.y[q] = *reinterpret_cast<const float4_u*>(in.y + e + 4 * q);
+            h.z[q] = *reinterpret_cast<const float4_u*>(in.z + e + 4 * q);
+            h.row[q] = *reinterpret_cast<const uint32_u*>(in.row + e + 4 * q);
+        }
         return;
     }
+    h.base = 0;
     uint32_t r[kChunk];
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-        const int c = kIdx ? h.c[k] : a + (k < n ? k : n - 1);
-        h.y[k] = in.y[c];
-        h.z[k] = in.z[c];
+        const int c = a + (k < n ? k : n - 1);
+        h.y[k / 4][k % 4] = in.y[c];
+        h.z[k / 4][k % 4] = in.z[c];
         r[k] = in.row[c];
     }
-    h.row = r[0] | r[1] << 8 | r[2] << 16 | r[3] << 24;
+#pragma unroll
+    for (int q = 0; q < kQuads; ++q)
+        h.row[q] = r[4 * q] | r[4 * q + 1] << 8 | r[4 * q + 2] << 16 | r[4 * q + 3] << 24;
 }
 
 // the chunk into the lane's LDS column (plane, y, z, reciprocal of plane
@@ -607,12 +605,68 @@ __device__ __forceinline__ bool put_chunk(const HitChunk& h, float4* col, const 
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-        const int r = (int)(h.row >> (8 * k)) & 255;
+        const int r = (int)(h.row[k / 4] >> (8 * (k % 4))) & 255;
         bad |= r >= n_rows;
         const float2 x = xs[r];
-        col[k * kWave] = make_float4(x.x, h.y[k], h.z[k], x.y);
+        col[k * kWave] = make_float4(x.x, h.y[k / 4][k % 4], h.z[k / 4][k % 4], x.y);
     }
     return bad;
+}
+
+// The same through an index: item j of a lane is hit lane % kChunk of the
+// chunk of track lane / kChunk + j * kWave / kChunk of the wave.
+constexpr int kItems = kChunk;
+
+struct GatherChunk {
+    int c[kItems];                  // clusters of the chunk to load next, -1 past the track
+    float y[kItems], z[kItems];
+    int r[kItems];                  // -1 past the track
+};
+
+__device__ __forceinline__ int gather_track(int j)
+{
+    return (int)(threadIdx.x & (kWave - 1)) / kChunk + j * (kWave / kChunk);
+}
+
+// a, n: entry and hits of the tracks of the lane's items
+__device__ __forceinline__ void gather_index(GatherChunk& h, const HitRows& in, const int* a,
+                                             const int* n, int i0)
+{
+    const int i = i0 + (int)(threadIdx.x & (kChunk - 1));
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        h.c[j] = -1;
+        if (i < n[j]) h.c[j] = in.idx[a[j] + i];
+    }
+}
+
+__device__ __forceinline__ void gather_hits(GatherChunk& h, const HitRows& in)
+{
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        h.r[j] = -1;
+        if (h.c[j] >= 0) {
+            h.r[j] = in.row[h.c[j]];
+            h.y[j] = in.y[h.c[j]];
+            h.z[j] = in.z[h.c[j]];
+        }
+    }
+}
+
+// into the tracks' LDS columns; flags a hit row outside the table in
+// bad[track]
+__device__ __forceinline__ void put_gather(const GatherChunk& h, float4* hits, int* bad,
+                                           const float2* xs, int n_rows)
+{
+    const int k = threadIdx.x & (kChunk - 1);
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        if (h.r[j] < 0) continue;
+        const int l = gather_track(j);
+        const float2 x = xs[h.r[j]];
+        if (h.r[j] >= n_rows) bad[l] = 1;
+        hits[k * kWave + l] = make_float4(x.x, h.y[j], h.z[j], x.y);
+    }
 }
 
 // ---- packed hits, with checkpoints ------------------------------------------
@@ -893,13 +947,15 @@ constexpr std::false_type kNo{};
 // where the forward pass reads its hits
 enum { kCsr = 0, kCsrIndex = 1, kPacked = 2 };
 
+// hits, bad: LDS of the readers without checkpoints
 template <int kFrom, bool kIn>
 __device__ __forceinline__ void refit_fwd(
-    const float* th, const float2* xs, float4* hits, const HitRows& in, const PackedHits& packed,
-    const int8_t* __restrict__ side, const int64_t* __restrict__ d_count, int64_t n_tracks,
-    int n_rows, const tpc_params& prm, const CalibModel& cm, float* __restrict__ par,
-    float* __restrict__ cov, float* __restrict__ chi2_out, int32_t* __restrict__ status,
-    float* __restrict__ ck, int stride, const int32_t* __restrict__ order)
+    const float* th, const float2* xs, float4* hits, int* badl, const HitRows& in,
+    const PackedHits& packed, const int8_t* __restrict__ side,
+    const int64_t* __restrict__ d_count, int64_t n_tracks, int n_rows, const tpc_params& prm,
+    const CalibModel& cm, float* __restrict__ par, float* __restrict__ cov,
+    float* __restrict__ chi2_out, int32_t* __restrict__ status, float* __restrict__ ck, int stride,
+    const int32_t* __restrict__ order)
 {
     constexpr bool kIdx = kFrom == kCsrIndex;
     const int lane = threadIdx.x & (kWave - 1);
@@ -985,18 +1041,35 @@ __device__ __forceinline__ void refit_fwd(
             for (int k = 0; k < parts; ++k)
                 bad |= packed.bad[(tb / kWave * parts + k) * kWave + lane] != 0;
         } else {
+            int aj[kItems], nj[kItems];
+            GatherChunk ng;
             HitChunk nx{};
-            if (ns > 0) {
-                if (kIdx) load_index(nx, in, a, n, 0);
-                load_chunk<kIdx>(nx, in, a, n, 0);
-                if (kIdx) load_index(nx, in, a, n, kChunk);
+            if (kIdx) {
+#pragma unroll
+                for (int j = 0; j < kItems; ++j) {
+                    aj[j] = __shfl(a, gather_track(j), kWave);
+                    nj[j] = __shfl(ns, gather_track(j), kWave);
+                }
+                gather_index(ng, in, aj, nj, 0);
+                gather_hits(ng, in);
+                gather_index(ng, in, aj, nj, kChunk);
+                badl[lane] = 0;
+                __syncthreads();
+            } else if (ns > 0) {
+                load_chunk(nx, in, a, n, 0);
             }
             for (int i0 = 0; i0 < M; i0 += kChunk) {
-                const int base = nx.base;
-                if (i0 < ns) bad |= put_chunk(nx, col, xs, n_rows);
-                if (i0 + kChunk < ns) {
-                    load_chunk<kIdx>(nx, in, a, n, i0 + kChunk);
-                    if (kIdx) load_index(nx, in, a, n, i0 + 2 * kChunk);
+                const int base = kIdx ? i0 : nx.base;
+                if (kIdx) {
+                    put_gather(ng, hits, badl, xs, n_rows);
+                    __syncthreads();
+                    if (i0 + kChunk < M) {
+                        gather_hits(ng, in);
+                        gather_index(ng, in, aj, nj, i0 + 2 * kChunk);
+                    }
+                } else {
+                    if (i0 < ns) bad |= put_chunk(nx, col, xs, n_rows);
+                    if (i0 + kChunk < ns) load_chunk(nx, in, a, n, i0 + kChunk);
                 }
                 auto cal = [&](int k, auto end) {
                     const float4 r = col[k * kWave];
@@ -1006,7 +1079,9 @@ __device__ __forceinline__ void refit_fwd(
                 const int i_hi = i0 + kChunk < M ? i0 + kChunk : M;
                 for (int i = i0 > 1 ? i0 : 1; i < i_hi; ++i)
                     if (alive && i < n) step(cal(i - base, kNo));
+                if (kIdx) __syncthreads();       // the next chunk goes to the same place
             }
+            if (kIdx) bad = badl[lane] != 0;
         }
         if (t < nt) {
             if (n < 3) stat = 1;
@@ -1040,13 +1115,14 @@ __global__ __launch_bounds__(kWave) void k_refit_fwd(
     __shared__ float th[16];
     __shared__ float2 xs[256];
     __shared__ float4 hits[kFrom == kPacked ? kWave : kChunk * kWave];
+    __shared__ int bad[kFrom == kCsrIndex ? kWave : 1];     // by track of the wave
     load_theta(d_theta, th);
     if (load_rows(row_x, n_rows, cm.TH, xs))
-        refit_fwd<kFrom, true>(th, xs, hits, in, packed, side, d_count, n_tracks, n_rows, prm, cm,
-                               par, cov, chi2_out, status, ck, stride, order);
+        refit_fwd<kFrom, true>(th, xs, hits, bad, in, packed, side, d_count, n_tracks, n_rows, prm,
+                               cm, par, cov, chi2_out, status, ck, stride, order);
     else
-        refit_fwd<kFrom, false>(th, xs, hits, in, packed, side, d_count, n_tracks, n_rows, prm, cm,
-                                par, cov, chi2_out, status, ck, stride, order);
+        refit_fwd<kFrom, false>(th, xs, hits, bad, in, packed, side, d_count, n_tracks, n_rows, prm,
+                                cm, par, cov, chi2_out, status, ck, stride, order);
 }
 
 // Hit gradients of kGrads slots leave together: 16 lanes write 16 entries of
