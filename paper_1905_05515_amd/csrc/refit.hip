@@ -16,8 +16,8 @@
 // gradient is reduced per block in a fixed order, then over blocks.
 //
 // What bounds them: few tracks, the serial chain of one track's hits, at 4.3
-// cycles per VALU instruction (forward 1.3 us a hit, then 0.85; adjoint 2.0,
-// then 1.55, on 400 tracks, with the short division and root sequences and
+// cycles per VALU instruction (forward 1.15 us a hit, then 0.9; adjoint 1.9,
+// then 1.6, on 400 tracks of up to 152 hits, with the short division and root sequences and
 // without waits for hits); many, the checkpoints (80 or 40 bytes a hit
 // written and read back) and then the adjoint's instructions.
 #include <algorithm>
@@ -716,7 +716,7 @@ __device__ __forceinline__ RawHit raw_at(const PackedCol& c, int i)
 // key counts (one wave's equal keys found by nine ballots), an exclusive scan
 // over (key, run), then every track's position.  What bounds it is the
 // launches and the counts: with one run per 256 tracks of the capacity, the
-// ordering and its scan took 64 us for the 17,000 tracks that 512 sectors
+// ordering and its scan took 64 us for the 79,000 tracks that 512 sectors
 // leave in buffers many times that size, and now 19; a million tracks take
 // 32 either way.
 constexpr int kOrdRanges = 512;
@@ -1321,7 +1321,7 @@ void k_refit_adj(
 // k sums parameter k; thread j adds partials j, j + 256, ... of it, then a
 // fixed tree.  Bound by the latency of the strided loads, so eight are in
 // flight, and the blocks past the count on the device (their partials are
-// zero) are left out: 33 us -> 4.4 for the 17,000 tracks of 512 sectors in
+// zero) are left out: 35 us -> 4.8 for the 79,000 tracks of 512 sectors in
 // their far larger buffers (16,384 blocks),
 // 34 -> 23 for a million.
 __global__ __launch_bounds__(kBlock) void k_reduce_theta(const double* __restrict__ partials,
@@ -1464,8 +1464,8 @@ static unsigned refit_grid(int64_t n_tracks)
 // 1170 + 2160 with every second; 100,000: 256 + 352, 180 + 357; 400, where
 // the adjoint's chain of instructions is what counts: 135 + 246, 122 + 290.
 // The line lies where the tracks' waves fill the SIMDs.  (A device count
-// below n_tracks does not move it: 17,000 tracks in buffers for 440,000 lose
-// 40 us in the adjoint and win 10 in the forward pass.)
+// below n_tracks does not move it: 16,783 tracks take 169 + 245 in buffers of
+// their own, 157 + 303 in buffers for 440,000.)
 constexpr int64_t kSparseTracks = int64_t(1) << 16;
 
 // The checkpoint buffer: the tiles, then the tile order (int32 per track),
