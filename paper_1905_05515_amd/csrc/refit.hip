@@ -17,9 +17,9 @@
 //
 // What bounds them: few tracks, the serial chain of one track's hits, at 4.3
 // cycles per VALU instruction (forward 1.15 us a hit, then 0.9; adjoint 1.9,
-// then 1.6, on 400 tracks of up to 152 hits, with the short division and root sequences and
-// without waits for hits); many, the checkpoints (80 or 40 bytes a hit
-// written and read back) and then the adjoint's instructions.
+// then 1.6, on 400 tracks of up to 152 hits, with the short division and root
+// sequences and without waits for hits); many, the checkpoints (80 or 40 bytes
+// a hit written and read back) and then the adjoint's instructions.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
